@@ -22,6 +22,8 @@
 //      then CholeskyQR2 of the K vectors (modified Gram-Schmidt when a pivot is
 //      not safely positive).
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 
@@ -67,12 +69,12 @@ __device__ __forceinline__ double half_sum(double x) {   // over each 32-lane ha
   return x;
 }
 
-// Data-parallel-primitive move of a double (both 32-bit halves with the same control).
+// Data-parallel-primitive move of a double (both 32-bit halves with the same control; every lane has a source).
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double x) {
   const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffLL), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)(b & 0xffffffffLL), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
@@ -86,19 +88,6 @@ __device__ __forceinline__ double row16_sum(double x) {
   return x;
 }
 
-// row16_sum of several independent values, stage by stage (the DPP chains overlap)
-template <int NV>
-__device__ __forceinline__ void row16_sum_n(double (&x)[NV]) {
-#pragma unroll
-  for (int v = 0; v < NV; ++v) x[v] += dpp_mov<0xB1>(x[v]);
-#pragma unroll
-  for (int v = 0; v < NV; ++v) x[v] += dpp_mov<0x4E>(x[v]);
-#pragma unroll
-  for (int v = 0; v < NV; ++v) x[v] += dpp_mov<0x141>(x[v]);
-#pragma unroll
-  for (int v = 0; v < NV; ++v) x[v] += dpp_mov<0x140>(x[v]);
-}
-
 __device__ __forceinline__ double lane_val(double x, int l) {   // x of lane l (l wave-uniform)
   const long long b = __double_as_longlong(x);
   const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), l);
@@ -106,10 +95,23 @@ __device__ __forceinline__ double lane_val(double x, int l) {   // x of lane l (
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Wave sum as a wave-uniform value (same order in every wave).
+// Sum of x over the wave, in every lane: rows of 16, then rows and halves
+// exchanged (each swap leaves the two operands' sums over both places).
 __device__ __forceinline__ double wave_sum_u(double x) {
   x = row16_sum(x);
-  return (lane_val(x, 0) + lane_val(x, 16)) + (lane_val(x, 32) + lane_val(x, 48));
+  long long b = __double_as_longlong(x);
+  int lo = (int)(unsigned)(b & 0xffffffffLL), hi = (int)(b >> 32);
+  auto l2 = __builtin_amdgcn_permlane16_swap(lo, lo, false, true);
+  auto h2 = __builtin_amdgcn_permlane16_swap(hi, hi, false, true);
+  x = __longlong_as_double(((long long)h2[0] << 32) | (unsigned)l2[0]) +
+      __longlong_as_double(((long long)h2[1] << 32) | (unsigned)l2[1]);
+  b = __double_as_longlong(x);
+  lo = (int)(unsigned)(b & 0xffffffffLL);
+  hi = (int)(b >> 32);
+  l2 = __builtin_amdgcn_permlane32_swap(lo, lo, false, true);
+  h2 = __builtin_amdgcn_permlane32_swap(hi, hi, false, true);
+  return __longlong_as_double(((long long)h2[0] << 32) | (unsigned)l2[0]) +
+         __longlong_as_double(((long long)h2[1] << 32) | (unsigned)l2[1]);
 }
 
 // Sum over the workgroup: wave sums, then every thread adds the wave partials in order.
@@ -461,566 +463,605 @@ __global__ __launch_bounds__(EIG_THREADS) void k_syev_topk(const double* __restr
   for (int j = tid; j < K; j += EIG_THREADS) lam_out[j] = lam[j];
 }
 
-// ---- K-hat <= 128: fused, register-resident variant --------------------------------------------
+// ---- K-hat <= 128: register-resident variant ----------------------------------------------------
 //
-// Lane l of every wave owns the columns J = l and J = l + 64.  Step k holds the
-// reflector v_k and w_k = p_k - (tau_k/2)(p_k.v_k) v_k in registers (zero for
-// J <= k).  One pass per step updates rows k+2.. of the trailing matrix with
-// reflector k and, on the updated values, accumulates the product p_{k+1} =
-// tau_{k+1} A v_{k+1} of the next reflector, which every wave builds from the
-// updated row k+1 on its own.  The eight waves' partial products meet in LDS
-// (double-buffered by step parity), so each step has a single barrier.
+// One workgroup of four waves, one per SIMD; what bounds it is the chain of
+// dependent FP64 operations, so each phase is laid out for a short chain and
+// few LDS reads.
+//
+//   1. Tridiagonalisation.  Wave w keeps rows I = 4u + w of the matrix in
+//      registers, lane l its columns J = l and l + 64.  Step k needs p = tau A v
+//      of the reflector built from x = row k.  With u = x - beta e_{k+1},
+//      v = u / (alpha - beta), the waves multiply A with the raw x in the same
+//      pass over the registers that applies reflector k - 1 (A x needs neither
+//      beta nor tau, so the norm's reduction, root and reciprocals run beside
+//      it), and A u = A x - beta A e_{k+1} follows from row k + 1, which its
+//      owner publishes.  The waves' partial products and that row meet in LDS
+//      (double-buffered by step parity): one barrier per step.  Every wave then
+//      forms v, w and the next x on its own, once with J over the lanes and
+//      once with the wave's own rows over the lanes of each 16-lane row, from
+//      where a 64-bit row broadcast hands v_I, w_I and x_I to the pass.
+//   2. Eigenvalues by multisection on the Sturm sequence of the leading
+//      principal minors, p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: two
+//      multiply-adds per step and no division.  T is scaled by a power of two to
+//      norm [1, 2) and e^2 floored at 1e-30 (a perturbation below 1e-15 of the
+//      norm), so that eight steps cannot underflow (each shrinks the pair
+//      (p_i, p_{i-1}) by at most e^2 / 6); the pair is rescaled every eighth step.
+//   3. Inverse iteration, lane j of one row of 16 for vector j.  What it needs is
+//      all the LDS holds beside the packed reflectors, so n up to 128 runs here.
+//   4. Back-transformation, a row of 16 lanes per vector, and, where
+//      eigenvalues are close, modified Gram-Schmidt over the rows, twice.
+//
+// Measured at n = 100, K = 10 (one launch): 354 -> 161 us against a form with the
+// matrix in LDS, eight waves, whose passes were bound by LDS reads (three
+// broadcast reads per row) and whose Sturm steps divided.  Of the 161:
+// tridiagonalisation 104, multisection 17, LU 17, solves 10, back-transformation
+// 12.  n = 25, K = 5: 76 -> 35.
 constexpr int SM_N = 128;
+constexpr int SM_WAVES = 4;
+constexpr int SM_THREADS = 64 * SM_WAVES;
 
 __device__ __forceinline__ double rl(double x, int l) { return lane_val(x, l); }
 
-// value at column J of a two-register row (J wave-uniform)
-__device__ __forceinline__ double col_of(const double (&x)[2], int J) { return rl(J < 64 ? x[0] : x[1], J & 63); }
-
 struct SmallLayout {
-  int64_t A, part, vec, d, e, e2, tau, scl, red, lam, Z, lu, gm, total;
+  int64_t v, d, e, tau, lam, Z, lu, part, row, total;
 };
 
-static SmallLayout small_layout(int n, int K) {
+// doubles of the packed reflectors: reflector k keeps columns from the 16-column
+// block of its first entry, k + 1
+__host__ __device__ constexpr int small_voff(int m, int NG) {
+  const int b = m >> 4, i = m & 15;
+  return 16 * (16 * (b * NG - b * (b - 1) / 2) + i * (NG - b));
+}
+
+static SmallLayout small_layout(int n) {
   SmallLayout L{};
+  const int NG = (n + 15) / 16;
   int64_t o = 0;
-  L.A = o; o += (int64_t)n * (n + 1);
-  L.part = o; o += 2 * EIG_WAVES * SM_N;
-  L.vec = o; o += 2 * 3 * SM_N;
-  L.d = o; o += n;
-  L.e = o; o += n;
-  L.e2 = o; o += n;
-  L.tau = o; o += n;
-  L.scl = o; o += n;
-  L.red = o; o += 64;
-  L.lam = o; o += 32;
-  L.Z = o; o += (int64_t)K * n;
-  L.lu = o; o += (int64_t)K * 5 * n;
-  L.gm = o; o += 2 * (int64_t)K * K + 2;
+  L.v = o; o += small_voff(n > 1 ? n - 1 : 1, NG);
+  L.d = o; o += SM_N + 16;
+  L.e = o; o += SM_N + 16;
+  L.tau = o; o += SM_N;
+  L.lam = o; o += 16;
+  L.Z = o; o += 16 * (int64_t)n;
+  // the LU factors share their place with the tridiagonalisation's buffers
+  L.lu = o;
+  L.part = o;
+  L.row = o + 2 * SM_WAVES * SM_N;
+  o += std::max<int64_t>(64 * (int64_t)n, 2 * SM_WAVES * SM_N + 3 * SM_N);
   L.total = o;
   return L;
 }
 
-// Reflector that maps the entries J >= j0 of a register row x to a multiple of
-// e_{j0}: beta, tau, scale and v (v_{j0} = 1, v_J = x_J * scale for J > j0, 0 below).
-__device__ __forceinline__ void reflector(const double (&x)[2], int j0, int n, double& beta, double& t, double& scale,
-                                          double (&v)[2]) {
-  const int lane = threadIdx.x & 63;
-  double s = 0.0;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int J = lane + 64 * c;
-    if (J > j0 && J < n) s += x[c] * x[c];
-  }
-  const double xn2 = wave_sum_u(s);
-  const double alpha = col_of(x, j0);
-  if (xn2 == 0.0) {
-    beta = alpha;
-    t = 0.0;
-    scale = 0.0;
-  } else {
-    beta = -copysign(sqrt(alpha * alpha + xn2), alpha);
-    // Newton-refined reciprocals: the two divisions sit on every step's critical path
-    double rb = __builtin_amdgcn_rcp(beta);
-    rb = fma(fma(-beta, rb, 1.0), rb, rb);
-    rb = fma(fma(-beta, rb, 1.0), rb, rb);
-    const double am = alpha - beta;
-    double ra = __builtin_amdgcn_rcp(am);
-    ra = fma(fma(-am, ra, 1.0), ra, ra);
-    ra = fma(fma(-am, ra, 1.0), ra, ra);
-    t = (beta - alpha) * rb;
-    scale = ra;
-  }
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int J = lane + 64 * c;
-    v[c] = J == j0 ? 1.0 : ((J > j0 && J < n) ? x[c] * scale : 0.0);
-  }
+// x of lane N of this lane's row of 16 (one 64-bit move)
+template <int N>
+__device__ __forceinline__ double row_bcast(double x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x150 + N, 0xf, 0xf, true);
 }
 
-// Sturm counts for the small kernel: q <- d_i - x - e_i^2 / q with a
-// Newton-refined hardware reciprocal (two steps after the estimate).
-// One Sturm count.
-__device__ __forceinline__ int sturm_count1(const double* d, const double* e2, int n, double x, double pivmin) {
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  int cnt = q < 0.0;
-  for (int i = 1; i < n; ++i) {
-    double r = __builtin_amdgcn_rcp(q);
-    r = fma(fma(-q, r, 1.0), r, r);
-    r = fma(fma(-q, r, 1.0), r, r);
-    q = fma(-e2[i - 1], r, d[i] - x);
-    if (fabs(q) < pivmin) q = -pivmin;
-    cnt += q < 0.0;
-  }
-  return cnt;
+// Newton-refined hardware reciprocal
+__device__ __forceinline__ double rcp2(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
 }
 
-// Two Sturm counts, interleaved, with the same arithmetic as sturm_count1.
-__device__ __forceinline__ void sturm_count2r(const double* d, const double* e2, int n, double x0, double x1,
-                                              double pivmin, int& c0, int& c1) {
-  double q0 = d[0] - x0, q1 = d[0] - x1;
-  if (fabs(q0) < pivmin) q0 = -pivmin;
-  if (fabs(q1) < pivmin) q1 = -pivmin;
-  c0 = q0 < 0.0;
-  c1 = q1 < 0.0;
-#pragma unroll 4
-  for (int i = 1; i < n; ++i) {
-    const double di = d[i], ei = e2[i - 1];
-    double r0 = __builtin_amdgcn_rcp(q0), r1 = __builtin_amdgcn_rcp(q1);
-    r0 = fma(fma(-q0, r0, 1.0), r0, r0);
-    r1 = fma(fma(-q1, r1, 1.0), r1, r1);
-    r0 = fma(fma(-q0, r0, 1.0), r0, r0);
-    r1 = fma(fma(-q1, r1, 1.0), r1, r1);
-    q0 = fma(-ei, r0, di - x0);
-    q1 = fma(-ei, r1, di - x1);
-    if (fabs(q0) < pivmin) q0 = -pivmin;
-    if (fabs(q1) < pivmin) q1 = -pivmin;
-    c0 += q0 < 0.0;
-    c1 += q1 < 0.0;
-  }
+// value at column J (wave-uniform) of a row held as NC registers
+template <int NC>
+__device__ __forceinline__ double col_of(const double (&x)[NC], int J) {
+  const double a = rl(x[0], J & 63), b = rl(x[NC - 1], J & 63);   // both read: a select of two registers
+  return J < 64 ? a : b;                                          // by index would put them in memory
 }
 
-__global__ __launch_bounds__(EIG_THREADS) void k_syev_small(const double* __restrict__ G, int n, int K, int Kout,
-                                                            SmallLayout L, double* __restrict__ lam_out,
-                                                            double* __restrict__ VK) {
-  extern __shared__ double sh[];
+// Calls f(integral constant 0 .. N-1).
+template <int... I, class F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+// NG: 16-row groups of the matrix (n <= 16 NG).
+template <int NG>
+__global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restrict__ G, int n, int K, int Kout,
+                                                           SmallLayout L, double* __restrict__ lam_out,
+                                                           double* __restrict__ VK) {
+  extern __shared__ __align__(16) double sh[];
+  constexpr int NC = NG <= 4 ? 1 : 2;     // columns per lane, and row-layout registers
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
-  const int S = n + 1;
-  double* A = sh + L.A;
-  double* part = sh + L.part;
-  double* vec = sh + L.vec;   // [v | w | v_next] of the current step, double-buffered by step parity
+  const int l16 = lane & 15;
+  double* V = sh + L.v;
   double* d = sh + L.d;
   double* e = sh + L.e;
-  double* e2 = sh + L.e2;
   double* tau = sh + L.tau;
-  double* scl = sh + L.scl;
-  double* red = sh + L.red;
   double* lam = sh + L.lam;
   double* Z = sh + L.Z;
-  double* lu = sh + L.lu;
-  double* gm = sh + L.gm;
 
-  for (int i = wave; i < n; i += EIG_WAVES)
-    for (int j = lane; j < n; j += 64) A[i * S + j] = G[(int64_t)i * n + j];
+  for (int i = tid; i < SM_N + 16; i += SM_THREADS) d[i] = e[i] = 0.0;
   __syncthreads();
 
   // 1. tridiagonalisation
-  if (n <= 2) {
-    if (tid == 0) {
-      d[0] = A[0];
-      e[0] = n == 2 ? A[1] : 0.0;
-      tau[0] = 0.0;
-      if (n == 2) { d[1] = A[S + 1]; e[1] = 0.0; tau[1] = 0.0; }
+  {
+    double* part = sh + L.part;
+    double* rowb = sh + L.row;
+    double a[NG * 4][NC];
+    int J[NC], Ir[NC];   // this lane's columns; its rows in the row layout
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      J[c] = lane + 64 * c;
+      Ir[c] = 4 * (l16 + 16 * c) + wave;
     }
-  } else {
-    double v[2], w[2], beta, t, scale;
-    {
-      double x[2];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int J = lane + 64 * c;
-        x[c] = J < n ? A[J] : 0.0;
-      }
-      reflector(x, 1, n, beta, t, scale, v);
-      double acc[2] = {0.0, 0.0};
-      for (int I = 1 + wave; I < n; I += EIG_WAVES) {
-        const double vI = col_of(v, I);
+    for (int u = 0; u < NG * 4; ++u) {
+      const int I = 4 * u + wave;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int J = lane + 64 * c;
-          if (J >= 1 && J < n) acc[c] += A[I * S + J] * vI;
+      for (int c = 0; c < NC; ++c) a[u][c] = (I < n && J[c] < n) ? G[(int64_t)I * n + J[c]] : 0.0;
+    }
+    double x[NC], xr[NC], v[NC], w[NC], nvr[NC], nwr[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      x[c] = (J[c] >= 1 && J[c] < n) ? G[J[c]] : 0.0;
+      xr[c] = (Ir[c] >= 1 && Ir[c] < n) ? G[Ir[c]] : 0.0;
+      v[c] = w[c] = nvr[c] = nwr[c] = 0.0;
+    }
+    double beta, t, scale;
+    // the reflector that maps the entries J >= j0 of x to beta e_{j0} (the
+    // identity when those past j0 are zero)
+    auto reflect = [&](int j0) __attribute__((always_inline)) {
+      double s = 0.0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s = fma(x[c], J[c] > j0 ? x[c] : 0.0, s);
+      const double xn2 = wave_sum_u(s);
+      const double alpha = col_of<NC>(x, j0);
+      // root of h = alpha^2 + xn2 from the hardware's 1 / sqrt(h), refined twice
+      const double h = fma(alpha, alpha, xn2);
+      double y = __builtin_amdgcn_rsq(h);
+      double g = h * y, hf = 0.5 * y;
+      double r = fma(-hf, g, 0.5);
+      g = fma(g, r, g);
+      hf = fma(hf, r, hf);
+      r = fma(-hf, g, 0.5);
+      g = fma(g, r, g);
+      hf = fma(hf, r, hf);
+      g = fma(fma(-g, g, h), hf, g);
+      const double bt = -copysign(g, alpha);
+      // factors 0 and 1, not selects of the results: those become a branch
+      const bool id = xn2 == 0.0;
+      const double on = id ? 0.0 : 1.0, am = id ? 1.0 : alpha - bt;
+      beta = id ? alpha : bt;
+      t = on * (am * copysign(2.0 * (id ? 1.0 : hf), alpha));
+      scale = on * rcp2(am);
+    };
+    // rows of the groups from G0 on: A -= v w^T + w v^T (UPD), acc = A x, both
+    // over the columns from C0 on; row kp, which lies in group G0, goes to the
+    // row buffer.  Waves that do not own it write to a spare one: no branches,
+    // so that the next reflector's chain runs among these multiply-adds.
+    auto pass = [&](auto upd, auto g0, int kp, int buf) __attribute__((always_inline)) {
+      constexpr bool UPD = decltype(upd)::value;
+      constexpr int G0 = decltype(g0)::value, C0 = G0 >= 5 ? NC - 1 : 0;
+      double acc[NC][2] = {};
+      static_for<4 * (NG - G0)>([&](auto ui) __attribute__((always_inline)) {
+        constexpr int u = decltype(ui)::value + 4 * G0, r = u >> 4, ln = u & 15;
+        const double xI = row_bcast<ln>(xr[r]);
+        if constexpr (UPD) {
+          const double vI = row_bcast<ln>(nvr[r]), wI = row_bcast<ln>(nwr[r]);
+#pragma unroll
+          for (int c = C0; c < NC; ++c) a[u][c] = fma(wI, v[c], fma(vI, w[c], a[u][c]));
+        }
+#pragma unroll
+        for (int c = C0; c < NC; ++c) acc[c][u & 1] = fma(a[u][c], xI, acc[c][u & 1]);
+      });
+      if constexpr (UPD) {
+        double* rb = rowb + ((kp & 3) == wave ? buf : 2) * SM_N;
+        const int q = (kp >> 2) & 3;
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+          const double a0 = a[4 * G0][c], a1 = a[4 * G0 + 1][c], a2 = a[4 * G0 + 2][c], a3 = a[4 * G0 + 3][c];
+          const double lo = q & 1 ? a1 : a0, hi = q & 1 ? a3 : a2;
+          rb[lane + 64 * c] = q & 2 ? hi : lo;
         }
       }
-      double* pb = part + EIG_WAVES * SM_N;   // the odd buffer: step 0 writes the even one
+      double* pb = part + (buf * SM_WAVES + wave) * SM_N;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) pb[wave * SM_N + lane + 64 * c] = acc[c];
+      for (int c = C0; c < NC; ++c) pb[lane + 64 * c] = acc[c][0] + acc[c][1];
+    };
+    using std::true_type;
+    using std::false_type;
+    // row 1 for step 0 comes the same way as the later ones
+    if (wave == 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) rowb[lane + 64 * c] = (n > 1 && J[c] < n) ? G[n + J[c]] : 0.0;
+    }
+    pass(false_type{}, std::integral_constant<int, 0>{}, 0, 0);
+    if (n >= 2) {
+      reflect(1);
+    } else {
+      beta = t = scale = 0.0;
+    }
+    if (tid == 0) {
+      d[0] = G[0];
+      e[0] = beta;
+      if (n == 2) d[1] = G[3];
+    }
+    double* const spare = rowb + 2 * SM_N + lane;   // where masked stores go
+    // step k, k + 2 in group G0
+    auto step = [&](auto g0, int k) __attribute__((always_inline)) {
+      constexpr int G0 = decltype(g0)::value, C0 = G0 >= 5 ? NC - 1 : 0;
+      const int buf = k & 1;
       __syncthreads();
+      // y = A x, and row k + 1 of A, in both layouts
+      double y[NC], yr[NC], rp[NC], rpr[NC];
+      const double* pb = part + buf * SM_WAVES * SM_N;
+      const double* rb = rowb + buf * SM_N;
+#pragma unroll
+      for (int c = C0; c < NC; ++c) {
+        double s[SM_WAVES];
+#pragma unroll
+        for (int ww = 0; ww < SM_WAVES; ++ww) s[ww] = pb[ww * SM_N + J[c]];
+        rp[c] = rb[J[c]];
+        y[c] = (s[0] + s[1]) + (s[2] + s[3]);
+      }
+#pragma unroll
+      for (int c = C0; c < NC; ++c) {
+        double s[SM_WAVES];
+#pragma unroll
+        for (int ww = 0; ww < SM_WAVES; ++ww) s[ww] = pb[ww * SM_N + Ir[c]];
+        rpr[c] = rb[Ir[c]];
+        yr[c] = (s[0] + s[1]) + (s[2] + s[3]);
+      }
+      const double ts = t * scale;
       double pv = 0.0;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        double sp = 0.0;
-        for (int ww = 0; ww < EIG_WAVES; ++ww) sp += pb[ww * SM_N + lane + 64 * c];
-        const double pc = t * sp;
-        w[c] = pc;
-        pv += pc * v[c];
+      for (int c = C0; c < NC; ++c) {
+        v[c] = J[c] == k + 1 ? 1.0 : x[c] * scale;   // x is zero up to column k
+        w[c] = J[c] > k ? ts * fma(-beta, rp[c], y[c]) : 0.0;
+        pv = fma(w[c], v[c], pv);
       }
+      // the reflector, for the back-transformation (every wave the same values)
+      const int vb = ((k + 1) >> 4) << 4;
+      double* vk = V + small_voff(k + 1, NG) - vb;
+#pragma unroll
+      for (int c = C0; c < NC; ++c) *(J[c] >= vb && J[c] < 16 * NG ? vk + J[c] : spare) = v[c];
+      *(lane == 0 ? tau + k : spare) = t;
       const double kc = 0.5 * t * wave_sum_u(pv);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) w[c] -= kc * v[c];
-      if (tid == 0) {
-        d[0] = A[0];
-        e[0] = beta;
-        tau[0] = t;
-        scl[0] = scale;
+      for (int c = C0; c < NC; ++c) w[c] = fma(-kc, v[c], w[c]);
+      const double wk1 = col_of<NC>(w, k + 1);
+#pragma unroll
+      for (int c = C0; c < NC; ++c) {
+        const double nx = rp[c] - fma(wk1, v[c], w[c]);   // row k + 1 after reflector k
+        *(J[c] == k + 1 ? d + k + 1 : spare) = nx;
+        x[c] = J[c] > k + 1 ? nx : 0.0;
       }
-    }
-    for (int k = 0; k + 2 < n; ++k) {
-      // row k+1 after reflector k (v_{k+1} = 1)
-      const double wk1 = col_of(w, k + 1);
-      double nr[2];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int J = lane + 64 * c;
-        nr[c] = (J >= k + 1 && J < n) ? A[(k + 1) * S + J] - (w[c] + wk1 * v[c]) : 0.0;
+      for (int c = C0; c < NC; ++c) {
+        const double vr = Ir[c] == k + 1 ? 1.0 : xr[c] * scale;
+        const double wr = fma(-kc, vr, Ir[c] > k ? ts * fma(-beta, rpr[c], yr[c]) : 0.0);
+        const double nx = rpr[c] - fma(wk1, vr, wr);
+        xr[c] = Ir[c] > k + 1 ? nx : 0.0;
+        nvr[c] = -vr;
+        nwr[c] = -wr;
       }
-      const bool next = k + 3 < n;   // reflector k+1 exists
-      double vn[2] = {0.0, 0.0}, bn = 0.0, tn = 0.0, sn = 0.0;
-      if (next) reflector(nr, k + 2, n, bn, tn, sn, vn);
-      // rows k+2.. : update with reflector k, accumulate A v_{k+1}
-      double acc[2] = {0.0, 0.0};
-      bool cok[2];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int J = lane + 64 * c;
-        cok[c] = J >= k + 2 && J < n;
-      }
-      // the row constants v_I, w_I, v_next_I come from LDS as broadcast reads:
-      // every wave stores the same vectors, and reads back only its own stores
-      double* vb = vec + (k & 1) * 3 * SM_N;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        vb[lane + 64 * c] = v[c];
-        vb[SM_N + lane + 64 * c] = w[c];
-        vb[2 * SM_N + lane + 64 * c] = vn[c];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // four rows per iteration: all loads are issued before the first store;
-      // lanes outside the trailing block load and store the row's unused
-      // padding column, so no load or store is predicated
-      int coff[2];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) coff[c] = cok[c] ? lane + 64 * c : n;
-      for (int I0 = k + 2 + wave; I0 < n; I0 += 4 * EIG_WAVES) {
-        double a[4][2], cv[4], cw[4], cn[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int I = I0 + u * EIG_WAVES;
-          const int Ic = I < n ? I : n - 1;
-#pragma unroll
-          for (int c = 0; c < 2; ++c) a[u][c] = A[Ic * S + coff[c]];
-          cv[u] = vb[Ic];
-          cw[u] = vb[SM_N + Ic];
-          cn[u] = vb[2 * SM_N + Ic];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int I = I0 + u * EIG_WAVES;
-          if (I < n) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-              const double x = a[u][c] - (cv[u] * w[c] + cw[u] * v[c]);
-              A[I * S + coff[c]] = x;
-              acc[c] += x * cn[u];
-            }
-          }
-        }
-      }
-      double* pb = part + (k & 1) * EIG_WAVES * SM_N;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) pb[wave * SM_N + lane + 64 * c] = acc[c];
-      __syncthreads();
-      if (wave == 0) {
-        // row k+1 keeps the next reflector's entries; the back-transformation reads them
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int J = lane + 64 * c;
-          if (J >= k + 2 && J < n) A[(k + 1) * S + J] = nr[c];
-        }
-        const double dk1 = col_of(nr, k + 1), ek1 = next ? bn : col_of(nr, k + 2);   // whole wave active
-        if (lane == 0) {
-          d[k + 1] = dk1;
-          e[k + 1] = ek1;
-          tau[k + 1] = next ? tn : 0.0;
-          scl[k + 1] = next ? sn : 0.0;
-        }
-      }
-      if (!next) break;
-      double pv = 0.0;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        double sp = 0.0;
-        for (int ww = 0; ww < EIG_WAVES; ++ww) sp += pb[ww * SM_N + lane + 64 * c];
-        const int J = lane + 64 * c;
-        const double pc = (J >= k + 2 && J < n) ? tn * sp : 0.0;
-        w[c] = pc;
-        pv += pc * vn[c];
-      }
-      const double kc = 0.5 * tn * wave_sum_u(pv);
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        w[c] -= kc * vn[c];
-        v[c] = vn[c];
-      }
-    }
+      reflect(k + 2);
+      *(lane == 0 ? e + k + 1 : spare) = beta;
+      pass(true_type{}, g0, k + 2, buf ^ 1);
+    };
+    static_for<NG>([&](auto g0) __attribute__((always_inline)) {
+      constexpr int G0 = decltype(g0)::value;
+      const int k1 = min(16 * G0 + 14, n - 2);
+      for (int k = max(16 * G0 - 2, 0); k < k1; ++k) step(g0, k);
+    });
     __syncthreads();
-    if (tid == 0) {
-      d[n - 1] = A[(n - 1) * S + (n - 1)];
-      e[n - 1] = 0.0;
-      tau[n - 1] = 0.0;
+    if (n >= 3 && tid == 0) d[n - 1] = rowb[(n & 1) * SM_N + n - 1];
+  }
+  __syncthreads();
+  // norm and Gershgorin interval of T (every wave, same order), then T scaled
+  // by a power of two to norm [1, 2)
+  double glo = 1e300, ghi = -1e300, tnorm = 0.0;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = lane + 64 * c;
+    if (i < n) {
+      const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
+      glo = fmin(glo, d[i] - r);
+      ghi = fmax(ghi, d[i] + r);
+      tnorm = fmax(tnorm, fabs(d[i]) + r);
     }
   }
-  __syncthreads();
-  for (int i = tid; i < n; i += EIG_THREADS) e2[i] = e[i] * e[i];
-  __syncthreads();
-
-  double glo = 1e300, ghi = -1e300, emax = 0.0, tnorm = 0.0;
-  for (int i = 0; i < n; ++i) {
-    const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
-    glo = fmin(glo, d[i] - r);
-    ghi = fmax(ghi, d[i] + r);
-    emax = fmax(emax, i + 1 < n ? e2[i] : 0.0);
-    tnorm = fmax(tnorm, fabs(d[i]) + r);
+  for (int off = 32; off > 0; off >>= 1) {
+    glo = fmin(glo, __shfl_xor(glo, off, 64));
+    ghi = fmax(ghi, __shfl_xor(ghi, off, 64));
+    tnorm = fmax(tnorm, __shfl_xor(tnorm, off, 64));
   }
+  const int ex = tnorm > 0.0 ? ilogb(tnorm) : 0;
+  __syncthreads();   // the unscaled entries have been read
+  for (int i = tid; i < n; i += SM_THREADS) {
+    d[i] = ldexp(d[i], -ex);
+    e[i] = i + 1 < n ? ldexp(e[i], -ex) : 0.0;
+  }
+  glo = ldexp(glo, -ex);
+  ghi = ldexp(ghi, -ex);
+  tnorm = ldexp(tnorm, -ex);
   const double eps = 2.220446049250313e-16;
-  const double pivmin = fmax(2.2250738585072014e-308, eps * eps * emax);
-  const double widen = 2.0 * eps * fmax(fabs(glo), fabs(ghi)) + pivmin;
+  const double widen = 4.0 * eps * fmax(fmax(fabs(glo), fabs(ghi)), 1.0);
   glo -= widen;
   ghi += widen;
+  // start vectors of the inverse iteration
+  for (int i = tid; i < 16 * n; i += SM_THREADS) Z[i] = start_entry(i & 15, i >> 4);
+  __syncthreads();
 
-  // 2. multisection, 16 lanes x 2 points per eigenvalue (33 sub-intervals per
-  // round) until the interval is below 1e-11 of the spectrum's scale: inverse
-  // iteration needs no more, and the eigenvalues only scale U's columns.  Two
-  // interleaved recurrences per lane: a Sturm step is a chain of dependent
-  // FP64 operations, so four points per lane cost twice the time of two for
-  // one more bit per round.
+  // 2. multisection until the interval is below 1e-11 of the norm: inverse
+  // iteration needs no more, and the eigenvalues only scale U's columns
   {
-    const int g = tid >> 4, q = tid & 15;
-    const int gbase = lane & ~15;
-    const unsigned long long gmask = 0xFFFFULL << gbase;
-    const double tol = 1e-11 * fmax(tnorm, pivmin);
-    const bool act = g < K;
+    // eigenvalues below x: sign changes of the sequence
+    auto count = [&](double xp) __attribute__((always_inline)) {
+      double pm = 0.0, pc = 1.0;
+      uint32_t sg = 0;
+      int cnt = 0;
+      auto one = [&](double di, double e2) __attribute__((always_inline)) {
+        const double pn = fma(di - xp, pc, -(e2 * pm));
+        pm = pc;
+        pc = pn;
+        sg = __builtin_amdgcn_alignbit(sg, (uint32_t)(__double_as_longlong(pn) >> 32), 31);
+      };
+      auto rescale = [&]() __attribute__((always_inline)) {
+        const int q = -__builtin_amdgcn_frexp_exp(fmax(fabs(pc), fabs(pm)));
+        pc = __builtin_amdgcn_ldexp(pc, q);
+        pm = __builtin_amdgcn_ldexp(pm, q);
+      };
+      for (int i0 = 0; i0 < n; i0 += 16) {
+        const double dr = d[i0 + l16], er = i0 + l16 > 0 ? e[i0 + l16 - 1] : 0.0;
+        const double e2r = fmax(er * er, 1e-30);
+        if (i0 + 16 <= n) {
+          static_for<16>([&](auto ii) __attribute__((always_inline)) {
+            constexpr int i = decltype(ii)::value;
+            one(row_bcast<i>(dr), row_bcast<i>(e2r));
+            if constexpr ((i & 7) == 7) rescale();
+          });
+          cnt += __popc((sg ^ (sg >> 1)) & 0xffffu);
+        } else {
+          const int m = n - i0;
+          static_for<16>([&](auto ii) __attribute__((always_inline)) {
+            constexpr int i = decltype(ii)::value;
+            if (i < m) {
+              one(row_bcast<i>(dr), row_bcast<i>(e2r));
+              if constexpr ((i & 7) == 7) rescale();
+            }
+          });
+          cnt += __popc((sg ^ (sg >> 1)) & ((1u << m) - 1));
+        }
+      }
+      return cnt;
+    };
+    const int MS = K <= 4 ? 64 : K <= 8 ? 32 : 16;   // lanes per eigenvalue, one point each
+    const int g = tid / MS, q = tid & (MS - 1);
+    const unsigned long long gmask = MS == 64 ? ~0ULL : ((1ULL << MS) - 1) << (lane & ~(MS - 1));
+    const double tol = 1e-11 * fmax(tnorm, 1.0);
     const int idx = n - 1 - g;
-    constexpr int NP = 32;
-    // joint first round: one point per thread over the whole interval serves
-    // every eigenvalue at once (the partial-product buffer is free by now)
-    int* cnt0 = reinterpret_cast<int*>(part);
-    const double h0 = (ghi - glo) / (double)(EIG_THREADS + 1);
-    cnt0[tid] = sturm_count1(d, e2, n, glo + h0 * (double)(tid + 1), pivmin);
+    // joint first round: one point per thread over the whole interval
+    int* cnt0 = reinterpret_cast<int*>(sh + L.part);
+    const double h0 = (ghi - glo) / (double)(SM_THREADS + 1);
+    cnt0[tid] = count(glo + h0 * (double)(tid + 1));
     __syncthreads();
-    int t0 = -1, t1 = EIG_THREADS - 1;   // largest t with cnt0[t] <= idx (counts rise with x)
+    int t0 = -1, t1 = SM_THREADS - 1;   // largest t with cnt0[t] <= idx (counts rise with x)
     while (t0 < t1) {
       const int mid = (t0 + t1 + 1) >> 1;
       if (cnt0[mid] <= idx) t0 = mid; else t1 = mid - 1;
     }
-    double a = t0 < 0 ? glo : glo + h0 * (double)(t0 + 1);
-    double b = t0 >= EIG_THREADS - 1 ? ghi : glo + h0 * (double)(t0 + 2);
+    double lo = t0 < 0 ? glo : glo + h0 * (double)(t0 + 1);
+    double hi = t0 >= SM_THREADS - 1 ? ghi : glo + h0 * (double)(t0 + 2);
     int rounds = 0;
-    for (double wd = h0; wd > tol && rounds < 32; wd /= (double)(NP + 1)) ++rounds;
-    for (int r = 0; r < rounds; ++r) {
-      const double h = (b - a) / (double)(NP + 1);
-      const double x0 = a + h * (double)(2 * q + 1), x1 = a + h * (double)(2 * q + 2);
-      int c0 = 0, c1 = 0;
-      if (act) sturm_count2r(d, e2, n, x0, x1, pivmin, c0, c1);
-      const int P = __popcll(__ballot(c0 <= idx) & gmask) + __popcll(__ballot(c1 <= idx) & gmask);
-      const double na = P == 0 ? a : a + h * (double)P;
-      const double nb = P == NP ? b : a + h * (double)(P + 1);
-      a = na;
-      b = nb;
+    for (double wd = h0; wd > tol && rounds < 32; wd /= (double)(MS + 1)) ++rounds;
+    // a wave with no eigenvalue of its own skips; within a wave all lanes count
+    if (wave * (64 / MS) < K) {
+      for (int r = 0; r < rounds; ++r) {
+        const double h = (hi - lo) / (double)(MS + 1);
+        const int cn = count(lo + h * (double)(q + 1));
+        const int P = __popcll(__ballot(cn <= idx) & gmask);
+        const double na = P == 0 ? lo : lo + h * (double)P;
+        const double nb = P == MS ? hi : lo + h * (double)(P + 1);
+        lo = na;
+        hi = nb;
+      }
+      if (g < K && q == 0) lam[g] = 0.5 * (lo + hi);
     }
-    if (act && q == 0) lam[g] = 0.5 * (a + b);
   }
   __syncthreads();
 
-  // 3. inverse iteration (as in the general kernel), one lane per vector.  The
-  // recurrences are sequential, so their operands are loaded in chunks of
-  // eight steps ahead of use (one LDS round trip per chunk instead of one
-  // per step), the pivot choice is a select, and divisions are a
-  // Newton-refined reciprocal.
-  const double tiny = eps * fmax(tnorm, pivmin);
-  for (int j = tid; j < K; j += EIG_THREADS) {
+  // 3. eigenvectors of T by inverse iteration, lane j of the first row of 16
+  // for vector j: one LU factorisation of T - lambda I with partial pivoting,
+  // two solves from the seeded start vector (the first forward elimination runs
+  // with the factorisation).  Step i of vector j keeps {1/u0, multiplier} and
+  // {u1/u0, u2/u0}; the multiplier's last bit says whether the rows were swapped.
+  if (tid < 16) {
+    const int j = min(tid, K - 1);
     double lj = lam[j];
+    const double sep = 10.0 * eps * fmax(tnorm, 1.0);
+    // separate (numerically) equal eigenvalues so the factorisations differ
     for (int i = 0; i < j; ++i)
-      if (fabs(lam[i] - lj) < 10.0 * eps * fmax(tnorm, 1e-300)) lj -= 10.0 * eps * fmax(tnorm, 1e-300);
-    double* ui = lu + (int64_t)j * 5 * n;
-    double* u1 = ui + n;
-    double* u2 = u1 + n;
-    double* ml = u2 + n;
-    double* pv = ml + n;
-    double* z = Z + (int64_t)j * n;
-    constexpr int CH = 8;
-    auto rcp = [](double x) {
-      double r = __builtin_amdgcn_rcp(x);
-      r = fma(fma(-x, r, 1.0), r, r);
-      return fma(fma(-x, r, 1.0), r, r);
-    };
-    // LU factorisation with partial pivoting of T - lj I; full chunks of CH
-    // steps carry no bounds checks (a branch per step costs more than the
-    // step), the remainder goes one step at a time
-    double a0 = d[0] - lj, a1 = n > 1 ? e[0] : 0.0, a2 = 0.0;
-    auto lu_step = [&](int i, double c, double ndl, double ns) __attribute__((always_inline)) {
-      const double nd = ndl - lj;
+      if (fabs(lam[i] - lj) < sep) lj -= sep;
+    double2* P = reinterpret_cast<double2*>(sh + L.lu) + tid;
+    double2* U = P + 16 * n;
+    double* z = Z + tid;
+    const double tiny = eps * fmax(tnorm, 1.0);
+    double a0 = d[0] - lj, a1 = e[0];
+    double cur = z[0];
+    auto lu_step = [&](int i, double c, double dn, double ns, double nz) __attribute__((always_inline)) {
+      const double nd = dn - lj;
       const bool sw = fabs(c) > fabs(a0);
       const double p0 = sw ? c : (a0 == 0.0 ? tiny : a0);
-      const double r = rcp(p0);
-      const double mlt = (sw ? a0 : c) * r;
-      const double y1 = sw ? nd : a1, y2 = sw ? ns : a2;   // the pivot row's entries
-      const double x1 = sw ? a1 : nd, x2 = sw ? a2 : ns;   // the other row's
-      ui[i] = r; u1[i] = y1; u2[i] = y2; ml[i] = mlt; pv[i] = sw ? 1.0 : 0.0;
-      a0 = x1 - mlt * y1;
-      a1 = x2 - mlt * y2;
-      a2 = 0.0;
+      const double r = rcp2(p0);
+      const double m0 = (sw ? a0 : c) * r;
+      const double y1 = sw ? nd : a1, x1 = sw ? a1 : nd;   // the pivot row's entry, the other row's
+      const long long mb = (__double_as_longlong(m0) & ~1LL) | (sw ? 1LL : 0LL);
+      P[16 * i] = double2{r, __longlong_as_double(mb)};
+      U[16 * i] = double2{y1 * r, sw ? ns * r : 0.0};
+      z[16 * i] = sw ? nz : cur;
+      cur = sw ? fma(-m0, nz, cur) : fma(-m0, cur, nz);
+      a0 = fma(-m0, y1, x1);
+      a1 = sw ? -(m0 * ns) : ns;
     };
-    const int nl = n - 1;                  // LU steps
-    const int nfull = nl / CH * CH;
-    for (int i0 = 0; i0 < nfull; i0 += CH) {
-      double ce[CH], cd[CH], cs[CH];
+    const int nl = n - 1;
+    int i0 = 0;
+    for (; i0 < nl; i0 += 16) {
+      // rows i0 .. i0+15 over the lanes (entries past the end are zero)
+      const double ce = e[i0 + tid], cd = d[i0 + 1 + tid], cs = i0 + 1 + tid < nl ? e[i0 + 1 + tid] : 0.0;
+      double nz[16];
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        ce[u] = e[i0 + u];
-        cd[u] = d[i0 + u + 1];
-        cs[u] = i0 + u + 1 < nl ? e[i0 + u + 1] : 0.0;
+      for (int i = 0; i < 16; ++i) nz[i] = z[16 * min(i0 + i + 1, nl)];
+      if (i0 + 16 <= nl) {
+        static_for<16>([&](auto ii) __attribute__((always_inline)) {
+          constexpr int i = decltype(ii)::value;
+          lu_step(i0 + i, row_bcast<i>(ce), row_bcast<i>(cd), row_bcast<i>(cs), nz[i]);
+        });
+      } else {
+        static_for<16>([&](auto ii) __attribute__((always_inline)) {
+          constexpr int i = decltype(ii)::value;
+          if (i0 + i < nl) lu_step(i0 + i, row_bcast<i>(ce), row_bcast<i>(cd), row_bcast<i>(cs), nz[i]);
+        });
       }
-#pragma unroll
-      for (int u = 0; u < CH; ++u) lu_step(i0 + u, ce[u], cd[u], cs[u]);
     }
-    for (int i = nfull; i < nl; ++i) lu_step(i, e[i], d[i + 1], i + 1 < nl ? e[i + 1] : 0.0);
     if (a0 == 0.0) a0 = tiny;
-    ui[n - 1] = rcp(a0); u1[n - 1] = 0.0; u2[n - 1] = 0.0; ml[n - 1] = 0.0; pv[n - 1] = 0.0;
-    for (int i = 0; i < n; ++i) z[i] = start_entry(j, i);
+    P[16 * nl] = double2{rcp2(a0), 0.0};
+    U[16 * nl] = double2{0.0, 0.0};
+    z[16 * nl] = cur;
+    constexpr int CH = 8;   // steps whose operands are loaded together
     for (int it = 0; it < 2; ++it) {
-      // forward elimination with the row interchanges
-      double cur = z[0];
-      auto fw_step = [&](int i, double nx, double mi, double p) __attribute__((always_inline)) {
-        const bool sw = p != 0.0;
-        z[i] = sw ? nx : cur;
-        cur = sw ? fma(-mi, nx, cur) : fma(-mi, cur, nx);
-      };
-      for (int i0 = 0; i0 < nfull; i0 += CH) {
-        double cz[CH], cm[CH], cp[CH];
+      if (it == 1) {   // forward elimination with the row interchanges
+        cur = z[0];
+        auto fw = [&](int i, double nz, double ml) __attribute__((always_inline)) {
+          const bool sw = __double_as_longlong(ml) & 1;
+          z[16 * i] = sw ? nz : cur;
+          cur = sw ? fma(-ml, nz, cur) : fma(-ml, cur, nz);
+        };
+        int i = 0;
+        for (; i + CH <= nl; i += CH) {
+          double nz[CH], ml[CH];
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          cz[u] = z[i0 + u + 1];
-          cm[u] = ml[i0 + u];
-          cp[u] = pv[i0 + u];
+          for (int s = 0; s < CH; ++s) { nz[s] = z[16 * (i + s + 1)]; ml[s] = P[16 * (i + s)].y; }
+#pragma unroll
+          for (int s = 0; s < CH; ++s) fw(i + s, nz[s], ml[s]);
         }
-#pragma unroll
-        for (int u = 0; u < CH; ++u) fw_step(i0 + u, cz[u], cm[u], cp[u]);
+        for (; i < nl; ++i) fw(i, z[16 * (i + 1)], P[16 * i].y);
+        z[16 * nl] = cur;
       }
-      for (int i = nfull; i < nl; ++i) fw_step(i, z[i + 1], ml[i], pv[i]);
-      z[n - 1] = cur;
-      // back substitution with U (three diagonals), then normalise
-      double z1 = 0.0, z2 = 0.0, nrm = 0.0;
-      auto bw_step = [&](int i, double zi, double a, double b, double r) __attribute__((always_inline)) {
-        const double sv = (zi - a * z1 - b * z2) * r;
-        z[i] = sv;
+      // back substitution
+      double z1 = 0.0, z2 = 0.0;
+      auto bw = [&](int i, double zi, double r, double2 u) __attribute__((always_inline)) {
+        const double s = fma(-u.x, z1, fma(-u.y, z2, zi * r));
+        z[16 * i] = s;
         z2 = z1;
-        z1 = sv;
-        nrm += sv * sv;
+        z1 = s;
       };
-      const int bfull = n / CH * CH;       // steps n-1 .. n-bfull in full chunks
-      for (int i0 = n - 1; i0 > n - 1 - bfull; i0 -= CH) {
-        double cz[CH], c1[CH], c2[CH], cr[CH];
+      int i = nl;
+      for (; i - CH + 1 >= 0; i -= CH) {
+        double zi[CH], r[CH];
+        double2 u[CH];
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          cz[u] = z[i0 - u];
-          c1[u] = u1[i0 - u];
-          c2[u] = u2[i0 - u];
-          cr[u] = ui[i0 - u];
-        }
+        for (int s = 0; s < CH; ++s) { zi[s] = z[16 * (i - s)]; r[s] = P[16 * (i - s)].x; u[s] = U[16 * (i - s)]; }
 #pragma unroll
-        for (int u = 0; u < CH; ++u) bw_step(i0 - u, cz[u], c1[u], c2[u], cr[u]);
+        for (int s = 0; s < CH; ++s) bw(i - s, zi[s], r[s], u[s]);
       }
-      for (int i = n - 1 - bfull; i >= 0; --i) bw_step(i, z[i], u1[i], u2[i], ui[i]);
-      nrm = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
-      for (int i = 0; i < n; ++i) z[i] *= nrm;
+      for (; i >= 0; --i) bw(i, z[16 * i], P[16 * i].x, U[16 * i]);
     }
   }
   __syncthreads();
 
-  // 4. back-transformation: half a wave per vector, every half-wave's vectors
-  // (K <= 16: at most two) in registers and reduced together, so the
-  // latency of one reflector's reductions is paid once for both; the next
-  // reflector's row is loaded while the current one is applied
+  // 4. back-transformation: row of 16 lanes q of wave w holds vector 4w + q,
+  // entry l16 + 16 t in z[t]
+  const int vec = 4 * wave + (lane >> 4);
+  double z[NG];
   {
-    const int half = lane >> 5, hl = lane & 31;
-    constexpr int NV = 2;
-    double z[NV][4];
-    bool on[NV];
+    double s = 0.0;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int j = 2 * wave + half + 2 * EIG_WAVES * v;
-      on[v] = j < K;
-      const double* zr = Z + (int64_t)(on[v] ? j : 0) * n;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int i = hl + 32 * c;
-        z[v][c] = (on[v] && i < n) ? zr[i] : 0.0;
-      }
+    for (int t = 0; t < NG; ++t) {
+      const int i = l16 + 16 * t;
+      z[t] = i < n && vec < K ? Z[16 * i + vec] : 0.0;
+      s = fma(z[t], z[t], s);
     }
-    int ic[4];
+    s = row16_sum(s);
+    s = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) ic[c] = min(hl + 32 * c, n - 1);
-    // reflector k's row, tau and scale are loaded one step ahead: LDS returns
-    // in order, so a wait for this step's operands never waits for the next
-    double xn[4], tn = 0.0, sn = 0.0;
-    if (n >= 3) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xn[c] = A[(n - 3) * S + ic[c]];
-      tn = tau[n - 3];
-      sn = scl[n - 3];
-    }
-    for (int k = n - 3; k >= 0; --k) {
-      double x[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) x[c] = xn[c];
-      const double t = tn, sc = sn;
-      if (k > 0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) xn[c] = A[(k - 1) * S + ic[c]];
-        tn = tau[k - 1];
-        sn = scl[k - 1];
-      }
-      if (t == 0.0) continue;
-      double vv[4], sv[NV];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int i = hl + 32 * c;
-        vv[c] = i == k + 1 ? 1.0 : ((i > k + 1 && i < n) ? x[c] * sc : 0.0);
-      }
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc += vv[c] * z[v][c];
-        sv[v] = acc;
-      }
-      // the vectors' row sums stage by stage, interleaved
-      row16_sum_n<NV>(sv);
-      // each half-wave's sum: its two rows of 16 lanes
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const double s0 = lane_val(sv[v], 0) + lane_val(sv[v], 16), s1 = lane_val(sv[v], 32) + lane_val(sv[v], 48);
-        const double sh = t * (half ? s1 : s0);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) z[v][c] -= sh * vv[c];
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      if (!on[v]) continue;
-      double* zr = Z + (int64_t)(2 * wave + half + 2 * EIG_WAVES * v) * n;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int i = hl + 32 * c;
-        if (i < n) zr[i] = z[v][c];
-      }
-    }
+    for (int t = 0; t < NG; ++t) z[t] *= s;
   }
-  __syncthreads();
+  if (4 * wave < K) {
+    // reflectors whose first entry m = k + 1 lies in 16-entry block b touch blocks b ..
+    static_for<NG>([&](auto bi) __attribute__((always_inline)) {
+      constexpr int b = NG - 1 - decltype(bi)::value, NB = NG - b;
+      const int mhi = min(16 * b + 15, n - 2), mlo = max(16 * b, 1);
+      if (mhi < mlo) return;
+      double vn[NB], tn;
+      auto fetch = [&](int m) __attribute__((always_inline)) {
+        const double* vk = V + small_voff(m, NG) + l16;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) vn[t] = vk[16 * t];
+        tn = tau[m - 1];
+      };
+      fetch(mhi);
+      for (int m = mhi; m >= mlo; --m) {
+        double vv[NB];
+        const double tk_ = tn;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) vv[t] = vn[t];
+        fetch(max(m - 1, mlo));   // one step ahead of its use
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+          if (t & 1) s1 = fma(vv[t], z[b + t], s1);
+          else s0 = fma(vv[t], z[b + t], s0);
+        }
+        const double s = -tk_ * row16_sum(s0 + s1);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) z[b + t] = fma(s, vv[t], z[b + t]);
+      }
+    });
+  }
   // inverse iteration leaves vectors of eigenvalues more than 1e-3 ||T|| apart
   // orthogonal to working accuracy; closer ones are orthonormalised together
   bool cluster = false;
   for (int j = 1; j < K; ++j) cluster |= fabs(lam[j - 1] - lam[j]) < 1e-3 * tnorm;
-  if (cluster) orth_rows(Z, K, n, gm, lu, red);
-  for (int t = tid; t < n * K; t += EIG_THREADS) {
-    const int i = t / K, j = t - i * K;
-    VK[(int64_t)i * Kout + j] = Z[(int64_t)j * n + i];
+  if (cluster) {
+    double* qb = sh + L.part;   // the current vector, double-buffered
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int j = 0; j < K; ++j) {
+        double* q = qb + (j & 1) * SM_N;
+        if (vec == j) {
+          double s = 0.0;
+#pragma unroll
+          for (int t = 0; t < NG; ++t) s = fma(z[t], z[t], s);
+          s = row16_sum(s);
+          s = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll
+          for (int t = 0; t < NG; ++t) {
+            z[t] *= s;
+            q[l16 + 16 * t] = z[t];
+          }
+        }
+        __syncthreads();
+        double qv[NG], s = 0.0;
+#pragma unroll
+        for (int t = 0; t < NG; ++t) {
+          qv[t] = q[l16 + 16 * t];
+          s = fma(qv[t], z[t], s);
+        }
+        s = vec > j ? row16_sum(s) : 0.0;
+#pragma unroll
+        for (int t = 0; t < NG; ++t) z[t] = fma(-s, qv[t], z[t]);
+      }
+      __syncthreads();
+    }
   }
-  for (int j = tid; j < K; j += EIG_THREADS) lam_out[j] = lam[j];
+  if (vec < K) {
+#pragma unroll
+    for (int t = 0; t < NG; ++t) {
+      const int i = l16 + 16 * t;
+      if (i < n) VK[(int64_t)i * Kout + vec] = z[t];
+    }
+  }
+  if (tid < K) lam_out[tid] = ldexp(lam[tid], ex);
 }
 
 void eig_topk_krylov(Ctx* c, const double* G, int n, int K, int Kout, double* lam_k, double* VK, int mode);
@@ -1036,15 +1077,24 @@ void eig_topk_dense(Ctx* c, const double* G, int n0, int K, double* lam_k, doubl
   const int Ke = K < n0 ? K : n0;
   TK_REQUIRE(Ke <= 32, TK_ERR_UNSUPPORTED, "eigensolve: more than 32 eigenpairs");
   const size_t lim = c->lds_per_block;
-  const SmallLayout SL = small_layout(n0, Ke);
+  const SmallLayout SL = small_layout(n0);
   const bool small = n0 <= SM_N && Ke <= 16 && (size_t)SL.total * 8 <= lim;
   const EigLayout L = eig_layout(n0, Ke);
   ensure(c, c->work, sizeof(double) * (size_t)(L.total + 16));
   if (K > Ke) TK_HIP(hipMemsetAsync(lam_k, 0, sizeof(double) * K, c->stream));
   double* ws = c->work.as<double>();
   if (small) {
-    hipLaunchKernelGGL(k_syev_small, dim3(1), dim3(EIG_THREADS), (size_t)SL.total * 8, c->stream, G, n0, Ke, K, SL,
-                       lam_k, VK);
+    switch ((n0 + 15) / 16) {
+#define TK_SMALL_CASE(NG)                                                                                       \
+      case NG:                                                                                                  \
+        hipLaunchKernelGGL(k_syev_small<NG>, dim3(1), dim3(SM_THREADS), (size_t)SL.total * 8, c->stream, G, n0, \
+                           Ke, K, SL, lam_k, VK);                                                               \
+        break;
+      TK_SMALL_CASE(1) TK_SMALL_CASE(2) TK_SMALL_CASE(3) TK_SMALL_CASE(4)
+      TK_SMALL_CASE(5) TK_SMALL_CASE(6) TK_SMALL_CASE(7) TK_SMALL_CASE(8)
+#undef TK_SMALL_CASE
+      default: fail(TK_ERR_UNSUPPORTED, "eigensolve: size out of range");
+    }
   } else if ((size_t)L.total * 8 <= lim) {
     hipLaunchKernelGGL(k_syev_topk<2>, dim3(1), dim3(EIG_THREADS), (size_t)L.total * 8, c->stream, G, n0, Ke, K, L,
                        ws, lam_k, VK);
@@ -1060,7 +1110,7 @@ void eig_topk_dense(Ctx* c, const double* G, int n0, int K, double* lam_k, doubl
 void eig_topk(Ctx* c, const double* G, int n0, int K, double* lam_k, double* VK, int mode) {
   const int Ke = K < n0 ? K : n0;
   TK_REQUIRE(Ke <= 32, TK_ERR_UNSUPPORTED, "eigensolve: more than 32 eigenpairs");
-  const SmallLayout SL = small_layout(n0, Ke);
+  const SmallLayout SL = small_layout(n0);
   const bool small = n0 <= SM_N && Ke <= 16 && (size_t)SL.total * 8 <= c->lds_per_block;
   if (!small && n0 >= KRYLOV_MIN_N && Ke <= 16) {
     eig_topk_krylov(c, G, n0, Ke, K, lam_k, VK, mode);
