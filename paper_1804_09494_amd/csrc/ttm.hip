@@ -7,8 +7,9 @@
 // rows of Y live in LDS for the whole bin; after the bin, rows of slices the
 // bin owns alone are written straight to Y and rows of slices split over
 // several bins go to a partial slot, which the fixup kernels sum in bin order.
-// Three kernels:
+// Four kernels:
 //   * k_ttm3_mfma: three modes, other ranks <= 16, on the matrix cores;
+//   * k_ttm3w_mfma: three modes, other ranks <= 32, one above 16, likewise;
 //   * k_ttm4_mfma: four modes, other ranks <= 16, on the matrix cores;
 //   * k_ttm_cols:  every other shape, on the vector ALUs.
 // None of them uses atomics: every sum runs in a fixed order.
@@ -439,6 +440,238 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
   }
 }
 
+// ---- three-mode TTM-chain with wide factors on the matrix cores ---------------------------------
+//
+// Three modes, both remaining ranks at most 32 and one of them above 16.
+// Y[row] as K_a x K_b is the same sum of (val F_a)^T F_b as above, covered by
+// TA x TB MFMA tiles (ceil(K_a / 16), ceil(K_b / 16)).  What bounds it is the
+// matrix cores (512 cycles per 16 elements with 2 x 2 tiles), so a few waves per
+// SIMD are enough and the bins may stay those of the vector-ALU kernel: a
+// workgroup of up to eight waves per bin, each wave taking a contiguous part.
+// Nothing of the bin is staged: a lane reads its element's coordinates and value
+// straight from the layout TTM3W_IDX blocks before their use, and its factor
+// rows TTM3_RING blocks before (16 bytes per lane and 16-column plane, four lanes
+// per row piece; a plane's columns past the row length re-read its last quad,
+// and only entries of Y beyond K_a or K_b come of them).  The planes go through
+// LDS (1 KB each) into operand layout.  A slice inside one wave's part goes
+// from the accumulators straight to Y or its partial slot; a slice that
+// continues into later waves meets in an LDS row of the wave where it ends: that
+// wave stores its piece, then the earlier ones add theirs in wave order (no
+// atomics, deterministic).
+//
+// Ranks 20 x 24 x 18, 8e6 elements: the three modes' chains with their fixup took
+// 3.13 ms with the vector-ALU kernel (one pass over the bin per 128 columns of Y,
+// a gathered factor entry per multiply) and take 0.87 ms here, 0.26 ms per
+// launch against 0.10 ms of matrix-core time.
+constexpr int TTM3W_WAVES = 8;
+
+template <int TA, int TB>
+__global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int nseg_pad) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int ka = A.Kj[0], kb = A.Kj[1], khat = A.khat;
+  const int64_t bin = xcd_bin(blockIdx.x, gridDim.x);
+  const int64_t e0 = A.bin_ptr[bin];
+  const int E = (int)(A.bin_ptr[bin + 1] - e0);   // multiple of 4
+  const int s0 = A.seg_ptr[bin];
+  const int nseg = A.seg_ptr[bin + 1] - s0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uni(tid >> 6), nw = uni(blockDim.x >> 6);
+  int* send = reinterpret_cast<int*>(smem);
+  int* sslot = send + nseg_pad;
+  int* srow = sslot + nseg_pad;
+  float* tile = reinterpret_cast<float*>(srow + nseg_pad) + wave * 256 * (TA + TB);
+  float* rows = reinterpret_cast<float*>(srow + nseg_pad) + nw * 256 * (TA + TB);   // nw x khat
+  for (int i = tid; i < nseg; i += blockDim.x) {
+    send[i] = (int)(A.seg_begin[s0 + i + 1] - e0);
+    sslot[i] = A.seg_slot[s0 + i];
+    srow[i] = A.seg_row[s0 + i];
+  }
+  __syncthreads();
+  const int Q = ((E + 16 * nw - 1) / (16 * nw)) * 16;   // elements per wave
+  const int cs = min(wave * Q, E), ce = min(cs + Q, E);
+  const int k = lane >> 4, cix = lane & 15;
+  floatx4_t C[TA][TB];
+  auto zero = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+      for (int b = 0; b < TB; ++b) C[a][b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  zero();
+  // the destination of segment sg's row, an offset from Y (a select of two
+  // pointers would become a private-memory table)
+  const uintptr_t ybase = reinterpret_cast<uintptr_t>(A.Y);
+  const uintptr_t pdiff = reinterpret_cast<uintptr_t>(A.partial) - ybase;
+  auto row_ptr = [&](int sg) __attribute__((always_inline)) {
+    const int slot = uni(sslot[sg]);
+    const int64_t r64 = slot < 0 ? uni(srow[sg]) : slot;
+    return ybase + (slot < 0 ? 0 : pdiff) + (uintptr_t)(r64 * khat) * 4;
+  };
+  // f(entry offset in the row, register quad, entries of it inside K_a) for every tile of this lane
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < TB; ++b) {
+      if (16 * b + cix >= kb) continue;
+#pragma unroll
+      for (int a = 0; a < TA; ++a) {
+        const int i0 = 16 * a + 4 * k;
+        if (i0 < ka) f(i0 + ka * (16 * b + cix), C[a][b], ka - i0);
+      }
+    }
+  };
+  const bool vec = (ka & 3) == 0;   // quads are whole and 16-byte aligned
+  int right_row = -1;               // the LDS row of the slice this wave leaves unfinished
+  if (cs < ce) {
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {   // first segment ending after cs
+      const int mid = (lo + hi) >> 1;
+      if (uni(send[mid]) > cs) hi = mid; else lo = mid + 1;
+    }
+    int sg = lo;
+    bool left = sg > 0 ? uni(send[sg - 1]) < cs : cs > 0;
+    int seg_hi = uni(send[sg]);
+    auto flush = [&]() __attribute__((always_inline)) {
+      if (seg_hi > ce) {   // continues into a later wave: stays in C
+        right_row = uni((seg_hi - 1) / Q);
+        return;
+      }
+      if (left) {          // begun by an earlier wave, ends here
+        float* r = rows + wave * khat;
+        each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q < n) r[o + q] = c[q];
+        });
+      } else {
+        const uintptr_t rp = row_ptr(sg);
+        if (vec) {
+          each([&](int o, const floatx4_t& c, int) __attribute__((always_inline)) {
+            __builtin_nontemporal_store(c, reinterpret_cast<__attribute__((address_space(1))) floatx4_t*>(rp + 4 * o));
+          });
+        } else {
+          each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+            auto* dst = reinterpret_cast<__attribute__((address_space(1))) float*>(rp + 4 * o);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (q < n) __builtin_nontemporal_store(c[q], dst + q);
+          });
+        }
+      }
+      left = false;
+      zero();
+    };
+    // block g: lane l takes element g + l/4 and quad l%4 of every plane.
+    // Reads past the wave's part are clamped to its last element (their
+    // steps are not run; a step never ends inside a quad of elements).
+    struct Idx { int a, b; float v; };
+    struct Blk { u32x4 x[TA], y[TB]; float v; };
+    const int* la = A.lay[0] + e0;
+    const int* lb = A.lay[1] + e0;
+    const float* lv = A.val + e0;
+    int oa[TA], ob[TB];
+#pragma unroll
+    for (int t = 0; t < TA; ++t) oa[t] = min(16 * t + 4 * (lane & 3), A.fstride[0] - 4);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) ob[t] = min(16 * t + 4 * (lane & 3), A.fstride[1] - 4);
+    auto fetch_idx = [&](int g, Idx& r) __attribute__((always_inline)) {
+      const int e = min(g + (lane >> 2), ce - 1);
+      r.a = __builtin_nontemporal_load(la + e);
+      r.b = __builtin_nontemporal_load(lb + e);
+      r.v = __builtin_nontemporal_load(lv + e);
+    };
+    auto fetch = [&](const Idx& i, Blk& r) __attribute__((always_inline)) {
+      const float* pa = A.F[0] + (int64_t)i.a * A.fstride[0];
+      const float* pb = A.F[1] + (int64_t)i.b * A.fstride[1];
+      r.v = i.v;
+#pragma unroll
+      for (int t = 0; t < TA; ++t) r.x[t] = *reinterpret_cast<const u32x4*>(pa + oa[t]);
+#pragma unroll
+      for (int t = 0; t < TB; ++t) r.y[t] = *reinterpret_cast<const u32x4*>(pb + ob[t]);
+    };
+    auto consume = [&](int g, const Blk& r) __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < TA; ++t)
+        reinterpret_cast<float4*>(tile + 256 * t)[lane] =
+            make_float4(__uint_as_float(r.x[t].x) * r.v, __uint_as_float(r.x[t].y) * r.v,
+                        __uint_as_float(r.x[t].z) * r.v, __uint_as_float(r.x[t].w) * r.v);
+#pragma unroll
+      for (int t = 0; t < TB; ++t) reinterpret_cast<u32x4*>(tile + 256 * (TA + t))[lane] = r.y[t];
+      wave_lds_sync();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int gu = g + 4 * u;
+        if (gu >= ce) break;
+        if (gu >= seg_hi) {   // a new slice starts at this step
+          flush();
+          ++sg;
+          seg_hi = uni(send[sg]);
+        }
+        float xa[TA], xb[TB];
+#pragma unroll
+        for (int t = 0; t < TA; ++t) xa[t] = tile[256 * t + (4 * u + k) * 16 + cix];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) xb[t] = tile[256 * (TA + t) + (4 * u + k) * 16 + cix];
+#pragma unroll
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+          for (int b = 0; b < TB; ++b)
+            C[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[a], xb[b], C[a][b], 0, 0, 0);
+      }
+      wave_lds_sync();   // the next block's write follows these reads
+    };
+    // indices run a ring ahead of the rows; every refill is unconditional and
+    // kept in issue order, so the wait before each block is for its own loads
+    static_assert(TTM3_RING == 3, "the ring steps below are written out for three blocks");
+    Idx ix[TTM3_RING];
+    Blk ring[TTM3_RING];
+#pragma unroll
+    for (int d = 0; d < TTM3_RING; ++d) fetch_idx(cs + 16 * d, ix[d]);
+#pragma unroll
+    for (int d = 0; d < TTM3_RING; ++d) {
+      fetch(ix[d], ring[d]);
+      fetch_idx(cs + 16 * (TTM3_RING + d), ix[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int g = cs; g < ce; g += 16 * TTM3_RING) {
+#pragma unroll
+      for (int d = 0; d < TTM3_RING; ++d) {
+        const int gg = g + 16 * d;
+        if (gg < ce) consume(gg, ring[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(ix[d], ring[d]);
+        fetch_idx(gg + 32 * TTM3_RING, ix[d]);
+      }
+    }
+    flush();
+  }
+  __syncthreads();
+  // pieces of slices that a later wave ended, added in wave order
+  for (int w = 0; w + 1 < nw; ++w) {
+    if (wave == w && right_row >= 0) {
+      float* r = rows + right_row * khat;
+      each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < n) r[o + q] += c[q];
+      });
+    }
+    __syncthreads();
+  }
+  if (cs > 0 && cs < ce) {   // the slice begun by an earlier wave that ended here
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (uni(send[mid]) > cs) hi = mid; else lo = mid + 1;
+    }
+    const bool left = lo > 0 ? uni(send[lo - 1]) < cs : true;
+    if (left && uni(send[lo]) <= ce) {
+      const uintptr_t rp = row_ptr(lo);
+      auto* dst = reinterpret_cast<__attribute__((address_space(1))) float*>(rp);
+      for (int c = lane; c < khat; c += 64) __builtin_nontemporal_store(rows[wave * khat + c], dst + c);
+    }
+  }
+}
+
 // ---- four-mode TTM-chain on the matrix cores ------------------------------------------------
 //
 // With remaining modes a, b, c (ascending), Y[row] viewed as K_a x (K_b K_c) is
@@ -790,6 +1023,23 @@ bool ttm_uses_mfma(int N, const int32_t* K, int n, const int* kp) {
   return true;
 }
 
+// Three-mode tensors with both remaining ranks <= 32 and one above 16 take the
+// wide matrix-core kernel (2 x 2 tiles waste up to three quarters of their
+// entries, at 17 x 17; at 20 x 24 x 18 they run 3.6 times as fast as the vector
+// ALUs, which gather a factor entry per multiply).  It reads the factor rows a quad at a
+// time, so their strides are multiples of four floats, as those of all factor
+// copies.
+bool ttm_uses_mfma3w(int N, const int32_t* K, int n, const int* kp) {
+  if (N != 3) return false;
+  bool wide = false;
+  for (int j = 0; j < 3; ++j) {
+    if (j == n) continue;
+    if (K[j] > 32 || kp[j] < K[j] || (kp[j] & 3) != 0) return false;
+    wide |= K[j] > 16;
+  }
+  return wide;
+}
+
 // The three-mode matrix-core kernel is the one ttm_run launches for mode n.
 bool ttm_takes_mfma3(const Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const int* kp) {
   if (pl.whole_slices || c->opt.ttm_kernel == TK_TTM_VECTOR) return false;
@@ -905,6 +1155,23 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
     } else {
       hipLaunchKernelGGL(k_ttm3_mfma<false>, dim3((unsigned)pl.P), dim3(64), lds, c->stream, a, Epad);
     }
+    TK_CHECK_LAUNCH();
+  } else if (!vector_only && ttm_uses_mfma3w(N, K, n, kp)) {
+    // waves per bin: at least 256 elements each
+    int nw = TTM3W_WAVES;
+    while (nw > 1 && 256 * nw > pl.E_pad_max) nw >>= 1;
+    const int TA = a.Kj[0] > 16 ? 2 : 1, TB = a.Kj[1] > 16 ? 2 : 1;
+    const int nseg_pad = (int)((pl.R_max + 3) & ~(int64_t)3);
+    const size_t lds = 3 * sizeof(int) * (size_t)nseg_pad +
+                       sizeof(float) * (size_t)nw * (256 * (size_t)(TA + TB) + (size_t)pl.khat);
+    TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
+    const dim3 g((unsigned)pl.P), b(64 * nw);
+    if (TA == 2 && TB == 2)
+      hipLaunchKernelGGL((k_ttm3w_mfma<2, 2>), g, b, lds, c->stream, a, nseg_pad);
+    else if (TA == 2)
+      hipLaunchKernelGGL((k_ttm3w_mfma<2, 1>), g, b, lds, c->stream, a, nseg_pad);
+    else
+      hipLaunchKernelGGL((k_ttm3w_mfma<1, 2>), g, b, lds, c->stream, a, nseg_pad);
     TK_CHECK_LAUNCH();
   } else if (!vector_only && ttm_uses_mfma4(N, K, n, kp)) {
     const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
