@@ -35,28 +35,43 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
 void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t n_obs, const int32_t* const* idx,
               tk_mem mem);
 
-void* Ctx::alloc_raw(size_t bytes) {
+void* Ctx::alloc_raw(size_t bytes, size_t* cap) {
   if (opt.mem_limit_bytes > 0 && bytes_in_use + (int64_t)bytes > opt.mem_limit_bytes)
     fail(TK_ERR_OOM, "allocation of " + std::to_string(bytes) + " bytes exceeds mem_limit_bytes");
   void* p = nullptr;
+  *cap = bytes;
   if (allocator.alloc) {
     p = allocator.alloc(bytes, allocator.user);
     if (!p) fail(TK_ERR_OOM, "the allocator hook returned no memory for " + std::to_string(bytes) + " bytes");
   } else {
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess || !p) {
-      (void)hipGetLastError();
-      fail(TK_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    if (caches()) {
+      *cap = BlockCache::round_up(bytes);
+      p = cache.take(*cap, stream, cap);
+    }
+    if (!p) {
+      hipError_t e = hipMalloc(&p, *cap);
+      if (e != hipSuccess && !cache.blocks.empty()) {   // give back what is kept, then once more
+        (void)hipGetLastError();
+        cache.trim(0, 0);
+        *cap = bytes;
+        e = hipMalloc(&p, *cap);
+      }
+      if (e != hipSuccess || !p) {
+        (void)hipGetLastError();
+        fail(TK_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+      }
     }
   }
   bytes_in_use += (int64_t)bytes;
   return p;
 }
 
-void Ctx::free_raw(void* p, size_t bytes) {
+void Ctx::free_raw(void* p, size_t bytes, size_t cap) {
   if (p) {
     if (allocator.free)
       allocator.free(p, bytes, allocator.user);
+    else if (caches())
+      cache.give(p, cap, stream);
     else
       (void)hipFree(p);
     bytes_in_use -= (int64_t)bytes;
@@ -352,6 +367,7 @@ tk_status tk_set_options(tk_ctx* c, const tk_options* o) {
     TK_REQUIRE(o->ttm_kernel >= TK_TTM_AUTO && o->ttm_kernel <= TK_TTM_FIBER, TK_ERR_INVALID_ARG, "ttm_kernel");
     TK_REQUIRE(o->eig_method >= TK_EIG_AUTO && o->eig_method <= TK_EIG_MATFREE, TK_ERR_INVALID_ARG, "eig_method");
     c->opt = *o;
+    if (!c->caches()) c->cache.trim(0, 0);
   });
 }
 

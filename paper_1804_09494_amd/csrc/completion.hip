@@ -75,6 +75,9 @@ void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t 
   int64_t pk = 1;
   for (int j = 0; j < N; ++j) pk *= ranks[j];
   o.G32.alloc(c, sizeof(float) * (size_t)pk);
+  o.Kd.alloc(c, sizeof(int32_t) * 8);
+  h2d(c, o.Kd.as<int32_t>(), o.K, 8);
+  c->sync();
   c->have_obs = true;
 }
 
@@ -233,7 +236,7 @@ void obs_eval(Ctx* c, const float* core, const float* const* F, float* model, tk
   const int N = o.N;
   int64_t pK = 1;
   for (int j = 0; j < N; ++j) pK *= o.K[j];
-  Buf tF[8], tG, tOut, tK(c, sizeof(int32_t) * 8);
+  Buf tF[8], tG, tOut;
   FPtrs fp{};
   IPtrs ip{};
   for (int j = 0; j < N; ++j) {
@@ -241,7 +244,6 @@ void obs_eval(Ctx* c, const float* core, const float* const* F, float* model, tk
     ip.p[j] = o.idx[j].as<int32_t>();
   }
   const float* G = dev_copy_f32(c, tG, core, (size_t)pK, mem);
-  h2d(c, tK.as<int32_t>(), o.K, 8);
   float* out = model;
   if (mem == TK_MEM_HOST) {
     tOut.alloc(c, sizeof(float) * (size_t)std::max<int64_t>(o.n_obs, 1));
@@ -272,10 +274,10 @@ void obs_eval(Ctx* c, const float* core, const float* const* F, float* model, tk
     const size_t lds = use_lds ? (size_t)pK * 4 : 0;
     if (o.K[0] <= 16)
       hipLaunchKernelGGL(k_eval<16>, dim3(grid_for(o.n_obs, 256, 8192)), dim3(256), lds, c->stream, fp, ip, N, o.K[0],
-                         tK.as<int32_t>(), G, o.n_obs, pK, use_lds, out);
+                         o.Kd.as<int32_t>(), G, o.n_obs, pK, use_lds, out);
     else
       hipLaunchKernelGGL(k_eval<64>, dim3(grid_for(o.n_obs, 256, 8192)), dim3(256), lds, c->stream, fp, ip, N, o.K[0],
-                         tK.as<int32_t>(), G, o.n_obs, pK, use_lds, out);
+                         o.Kd.as<int32_t>(), G, o.n_obs, pK, use_lds, out);
     TK_CHECK_LAUNCH();
   }
   if (mem == TK_MEM_HOST) d2h(c, model, out, (size_t)o.n_obs);
@@ -437,8 +439,7 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
   const int N = o.N;
   int64_t pK = 1;
   for (int j = 0; j < N; ++j) pK *= o.K[j];
-  Buf tF[8], tG, tg, tK(c, sizeof(int32_t) * 8);
-  h2d(c, tK.as<int32_t>(), o.K, 8);
+  Buf tF[8], tG, tg;
   for (int j = 0; j < N; ++j) {
     const float* src = dev_copy_f32(c, tF[j], F[j], (size_t)o.dims[j] * o.K[j], mem);
     hipLaunchKernelGGL(k_pad_copy, dim3(grid_for(o.dims[j] * o.kp[j], 256)), dim3(256), 0, c->stream, src, o.dims[j],
@@ -481,7 +482,7 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
       ensure(c, c->U64, sizeof(double) * (size_t)pl.L_nz * Kn);
       double* W = c->small64.as<double>();
       hipLaunchKernelGGL(k_core_unfold_t, dim3(grid_for((int64_t)khat * Kn, 256, 256)), dim3(256), 0, c->stream, G, N,
-                         tK.as<int32_t>(), n, khat, W);
+                         o.Kd.as<int32_t>(), n, khat, W);
       TK_CHECK_LAUNCH();
       uw_product(c, Yg, pl.L_nz, khat, W, Kn, c->U64.as<double>(), W + (size_t)khat * Kn);
       hipLaunchKernelGGL(k_scatter_rows, dim3(grid_for(pl.L_nz * Kn, 256)), dim3(256), 0, c->stream,
@@ -491,7 +492,7 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
       const size_t lds = sizeof(float) * (size_t)o.K[n] * khat;
       TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "adjoint: K_n x Khat too large for LDS");
       hipLaunchKernelGGL(k_dF, dim3(grid_for(pl.L_nz * o.K[n], 256, 16384)), dim3(256), lds, c->stream, Yg, pl.L_nz,
-                         khat, G, N, tK.as<int32_t>(), n, pl.row_slice.as<int32_t>(), dFn);
+                         khat, G, N, o.Kd.as<int32_t>(), n, pl.row_slice.as<int32_t>(), dFn);
       TK_CHECK_LAUNCH();
     }
     if (mem == TK_MEM_HOST) d2h(c, dF[n], dFn, (size_t)o.dims[n] * o.K[n]);
@@ -507,15 +508,14 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
         const int ntiles = (khat + 15) >> 4;
         const int64_t rpw = std::max<int64_t>(256, ceil_div(ceil_div(pl.L_nz, 512), 4) * 4);
         const int nwg = (int)ceil_div(pl.L_nz, rpw);
-        Buf part(c, sizeof(float) * (size_t)nwg * ntiles * 256);
+        ensure(c, o.part, sizeof(float) * (size_t)nwg * ntiles * 256);
         hipLaunchKernelGGL(k_dcore_mfma, dim3(nwg, (unsigned)ceil_div(ntiles, 4)), dim3(256), 0, c->stream, Yg,
                            pl.L_nz, khat, o.F32[0].as<float>(), o.kp[0], pl.row_slice.as<int32_t>(), rpw,
-                           part.as<float>());
+                           o.part.as<float>());
         TK_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_dcore_sum, dim3(grid_for(pK, 256)), dim3(256), 0, c->stream, part.as<float>(), nwg,
+        hipLaunchKernelGGL(k_dcore_sum, dim3(grid_for(pK, 256)), dim3(256), 0, c->stream, o.part.as<float>(), nwg,
                            khat, o.K[0], dc);
         TK_CHECK_LAUNCH();
-        c->sync();
       } else if (pl.L_nz > 0) {
         hipLaunchKernelGGL(k_dcore, dim3(grid_for(pK, 256)), dim3(256), 0, c->stream, Yg, pl.L_nz, khat,
                            o.F32[0].as<float>(), o.K[0], o.kp[0], pl.row_slice.as<int32_t>(), dc);
@@ -525,10 +525,9 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
         TK_CHECK_LAUNCH();
       }
       if (mem == TK_MEM_HOST) d2h(c, dcore, dc, (size_t)pK);
-      c->sync();
     }
-    c->sync();
   }
+  c->sync();   // the caller's inputs have been read
 }
 
 }  // namespace tk

@@ -370,6 +370,16 @@ static T fetch(Ctx* c, const T* d) {
   return h;
 }
 
+// *a + *b in one wait: a scan's last value and the last scanned entry
+template <class T>
+static int64_t fetch_sum(Ctx* c, const T* a, const T* b) {
+  T h[2] = {};
+  d2h(c, &h[0], a, 1);
+  d2h(c, &h[1], b, 1);
+  c->sync();
+  return (int64_t)h[0] + (int64_t)h[1];
+}
+
 static void build_plan_coarse(Ctx* c, ModePlan& pl, int N, int n, int64_t L, int64_t m, Buf* idx, const float* vals,
                               bool keep_order, const int32_t* order, Buf& skey, Buf& sperm, Buf& sstart, Buf& count,
                               Buf& row_of);
@@ -415,7 +425,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
                      count.as<int64_t>(), nonempty.as<int32_t>(), L);
   TK_CHECK_LAUNCH();
   exclusive_scan_i32(c, nonempty.as<int32_t>(), row_of.as<int32_t>(), L);
-  const int64_t Lnz = (int64_t)fetch(c, row_of.as<int32_t>() + L - 1) + fetch(c, nonempty.as<int32_t>() + L - 1);
+  const int64_t Lnz = fetch_sum(c, row_of.as<int32_t>() + L - 1, nonempty.as<int32_t>() + L - 1);
   pl.L_nz = Lnz;
   nonempty.release();
   const int64_t Lnz1 = Lnz > 0 ? Lnz : 1;
@@ -476,7 +486,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   if (n2 > 0) {
     // X = exclusive scan of sizes[t_hat..], with X[n2] = M2
     exclusive_scan_i64(c, size64.as<int64_t>() + t_hat, X.as<int64_t>(), n2);
-    M2 = fetch(c, X.as<int64_t>() + n2 - 1) + fetch(c, size64.as<int64_t>() + Lnz - 1);
+    M2 = fetch_sum(c, X.as<int64_t>() + n2 - 1, size64.as<int64_t>() + Lnz - 1);
   }
   h2d(c, X.as<int64_t>() + n2, &M2, 1);
   c->sync();
@@ -494,14 +504,16 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   pl.bin_ptr.alloc(c, 8 * (size_t)(P + 1));
   exclusive_scan_i64(c, load.as<int64_t>(), pl.bin_ptr.as<int64_t>(), P);
   h2d(c, pl.bin_ptr.as<int64_t>() + P, &m, 1);
-  Buf seg_first(c, 8 * (size_t)(P + 1)), mx(c, 8);
+  Buf seg_first(c, 8 * (size_t)(P + 1)), mx(c, 16);
   exclusive_scan_i64(c, nseg.as<int64_t>(), seg_first.as<int64_t>(), P);
-  const int64_t S = fetch(c, seg_first.as<int64_t>() + P - 1) + fetch(c, nseg.as<int64_t>() + P - 1);
-  pl.S = S;
   reduce_max_i64(c, nseg.as<int64_t>(), mx.as<int64_t>(), P);
-  pl.R_max = fetch(c, mx.as<int64_t>());
-  reduce_max_i64(c, load.as<int64_t>(), mx.as<int64_t>(), P);
-  pl.E_max = fetch(c, mx.as<int64_t>());
+  reduce_max_i64(c, load.as<int64_t>(), mx.as<int64_t>() + 1, P);
+  int64_t mx_h[2] = {0, 0};
+  d2h(c, mx_h, mx.as<int64_t>(), 2);
+  const int64_t S = fetch_sum(c, seg_first.as<int64_t>() + P - 1, nseg.as<int64_t>() + P - 1);
+  pl.S = S;
+  pl.R_max = mx_h[0];
+  pl.E_max = mx_h[1];
   TK_REQUIRE(pl.R_max <= cap, TK_ERR_DEVICE, "Lite partition: a bin holds more slices than the LDS row budget");
   TK_REQUIRE(S < ((int64_t)1 << 31), TK_ERR_UNSUPPORTED, "too many segments");
 
@@ -532,7 +544,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   hipLaunchKernelGGL(k_seg_slot, dim3(grid_for(S, B)), dim3(B), 0, c->stream, bad.as<int32_t>(),
                      slot_scan.as<int32_t>(), S, pl.seg_slot.as<int32_t>());
   TK_CHECK_LAUNCH();
-  pl.n_slots = S > 0 ? (int64_t)fetch(c, slot_scan.as<int32_t>() + S - 1) + fetch(c, bad.as<int32_t>() + S - 1) : 0;
+  pl.n_slots = S > 0 ? fetch_sum(c, slot_scan.as<int32_t>() + S - 1, bad.as<int32_t>() + S - 1) : 0;
   // bad slices
   int64_t nbad = 0;
   pl.fix_n.clear();
@@ -543,7 +555,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
                        last_seg.as<int64_t>(), n2, bflag.as<int32_t>());
     TK_CHECK_LAUNCH();
     exclusive_scan_i32(c, bflag.as<int32_t>(), bscan.as<int32_t>(), n2);
-    nbad = (int64_t)fetch(c, bscan.as<int32_t>() + n2 - 1) + fetch(c, bflag.as<int32_t>() + n2 - 1);
+    nbad = fetch_sum(c, bscan.as<int32_t>() + n2 - 1, bflag.as<int32_t>() + n2 - 1);
     pl.bad_row.alloc(c, 4 * (size_t)(nbad > 0 ? nbad : 1));
     pl.bad_slot.alloc(c, 4 * (size_t)(nbad + 1));
     int32_t zero = 0;
@@ -606,7 +618,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
                        plen.as<int64_t>());
     TK_CHECK_LAUNCH();
     exclusive_scan_i64(c, plen.as<int64_t>(), pl.seg_pbegin.as<int64_t>(), S);
-    pl.m_pad = S > 0 ? fetch(c, pl.seg_pbegin.as<int64_t>() + S - 1) + fetch(c, plen.as<int64_t>() + S - 1) : 0;
+    pl.m_pad = S > 0 ? fetch_sum(c, pl.seg_pbegin.as<int64_t>() + S - 1, plen.as<int64_t>() + S - 1) : 0;
     h2d(c, pl.seg_pbegin.as<int64_t>() + S, &pl.m_pad, 1);
     c->sync();
     pl.bin_pptr.alloc(c, 8 * (size_t)(P + 1));
@@ -721,7 +733,7 @@ static void build_plan_coarse(Ctx* c, ModePlan& pl, int N, int n, int64_t L, int
                        plen.as<int64_t>());
     TK_CHECK_LAUNCH();
     exclusive_scan_i64(c, plen.as<int64_t>(), pl.seg_pbegin.as<int64_t>(), S);
-    pl.m_pad = S > 0 ? fetch(c, pl.seg_pbegin.as<int64_t>() + S - 1) + fetch(c, plen.as<int64_t>() + S - 1) : 0;
+    pl.m_pad = S > 0 ? fetch_sum(c, pl.seg_pbegin.as<int64_t>() + S - 1, plen.as<int64_t>() + S - 1) : 0;
     h2d(c, pl.seg_pbegin.as<int64_t>() + S, &pl.m_pad, 1);
     c->sync();
     pl.bin_pptr.alloc(c, 8 * (size_t)(P + 1));
