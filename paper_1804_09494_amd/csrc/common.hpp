@@ -164,6 +164,7 @@ struct ModePlan {
   int64_t m_pad = 0;      // padded layout length
   int64_t E_pad_max = 0;  // largest padded bin
   Buf bin_pptr;           // int64[P+1]   padded bin offsets
+  Buf bin_order;          // uint32[P]    launch order of the bins (none: as they are)
   Buf seg_pbegin;         // int64[S+1]   padded segment offsets
   Buf order_pad;          // uint32[m_pad] element index at each padded position (0xffffffff = padding)
   Buf bad_row;            // int32[n_bad]

@@ -43,7 +43,7 @@ template <int NO>
 __global__ __launch_bounds__(256) void k_ttm_cols(TtmArgs A) {
   extern __shared__ __align__(16) float lds[];
   const int no = NO > 0 ? NO : A.n_other;
-  const int64_t bin = xcd_bin(blockIdx.x, gridDim.x);
+  const int64_t bin = launch_bin(A);
   const int col0 = blockIdx.y * TTMV_TILE;
   const int khat = A.khat;
   const int64_t e0 = A.bin_ptr[bin];
@@ -235,7 +235,7 @@ template <bool BFM, bool GATHER = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_ttm3_mfma(TtmArgs A, int Epad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int ka = A.KA, kb = A.KW;
-  const int64_t bin = xcd_bin(blockIdx.x, gridDim.x);
+  const int64_t bin = launch_bin(A);
   const int64_t e0 = A.bin_ptr[bin];
   const int E = (int)(A.bin_ptr[bin + 1] - e0);   // multiple of 4
   const int s0 = A.seg_ptr[bin];
@@ -469,7 +469,7 @@ template <int TA, int TB>
 __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int nseg_pad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int ka = A.Kj[0], kb = A.Kj[1], khat = A.khat;
-  const int64_t bin = xcd_bin(blockIdx.x, gridDim.x);
+  const int64_t bin = launch_bin(A);
   const int64_t e0 = A.bin_ptr[bin];
   const int E = (int)(A.bin_ptr[bin + 1] - e0);   // multiple of 4
   const int s0 = A.seg_ptr[bin];
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 8 ? 3
     TtmArgs A, int Epad, int nseg_pad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int ka = A.Kj[0], kb = A.Kj[1], kbc = A.Kj[1] * A.Kj[2];
-  const int64_t bin = xcd_bin(blockIdx.x, gridDim.x);
+  const int64_t bin = launch_bin(A);
   const int64_t e0 = A.bin_ptr[bin];
   const int E = (int)(A.bin_ptr[bin + 1] - e0);   // multiple of 4
   const int s0 = A.seg_ptr[bin];
@@ -1101,6 +1101,7 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
              const float* lay_val, int64_t m, float* Y, bool bf16, float* partial, const uint32_t* val_order) {
   TtmArgs a{};
   a.bin_ptr = pl.bin_pptr.as<int64_t>();
+  a.bin_order = pl.bin_order.as<uint32_t>();
   a.seg_ptr = pl.seg_ptr.as<int32_t>();
   a.seg_row = pl.seg_row.as<int32_t>();
   a.seg_begin = pl.seg_pbegin.as<int64_t>();

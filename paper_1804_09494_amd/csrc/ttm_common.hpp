@@ -12,6 +12,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct TtmArgs {
   const int64_t* bin_ptr;
+  const uint32_t* bin_order;  // launch order of the bins (null: as they are)
   const int32_t* seg_ptr;
   const int32_t* seg_row;
   const int64_t* seg_begin;
@@ -56,6 +57,12 @@ __device__ __forceinline__ int64_t xcd_bin(int64_t b, int64_t G) {
   const int64_t q = G >> 3, r = G & 7;
   const int64_t x = b & 7, i = b >> 3;
   return x * q + (x < r ? x : r) + i;
+}
+
+// The bin of this workgroup: consecutive places of the launch order on one XCD.
+__device__ __forceinline__ int64_t launch_bin(const TtmArgs& A) {
+  const int64_t i = xcd_bin(blockIdx.x, gridDim.x);
+  return A.bin_order ? (int64_t)A.bin_order[i] : i;
 }
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
