@@ -236,6 +236,7 @@ struct ObsSet {
   Buf G32;           // float[prod K] core copy
   Buf Kd;            // int32[8] the ranks
   Buf part;          // float: partial tiles of dG
+  Buf eval_pos;      // uint32[n_obs] layout position of each observation (two-pass forward)
 };
 
 struct Ctx {

@@ -26,6 +26,35 @@ __global__ void k_obs_validate(const int32_t* __restrict__ idx, int64_t m, int64
   if (bad) atomicOr(flag, 1);
 }
 
+// Place of block b among n: blocks go to the 8 XCDs round robin, each takes a
+// contiguous range.
+__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t n) {
+  const int64_t q = n >> 3, r = n & 7, x = b & 7;
+  return x * q + (x < r ? x : r) + (b >> 3);
+}
+
+static bool eval_on_mfma(const ObsSet& o) { return o.N == 3 && o.K[0] <= 16 && o.K[1] <= 16 && o.K[2] <= 16; }
+
+// the mode whose slices the three-mode forward walks
+static int eval_mode(const ObsSet& o) {
+  int mc = 0;
+  for (int j = 1; j < 3; ++j)
+    if (o.plan[j].L_nz < o.plan[mc].L_nz) mc = j;
+  return mc;
+}
+
+// With this many observations and at most that many slices the three-mode
+// forward writes its values in layout order and a second pass takes them to the
+// observations' own places: scattered 4-byte writes were half of its time, and
+// the second pass walks the observations in order, so it reads each slice's
+// values in order, from lines that stay in L2 while there are few slices
+// (5e7 observations in 50000 slices 2.34 -> 1.39 ms, 3.5e7 in 113 1.55 -> 0.91,
+// 1e7 in 1650 0.52 -> 0.29; 3e7 spread evenly over 300000 1.69 -> 1.78).
+constexpr int64_t EVAL_TWO_PASS = (int64_t)1 << 20;
+constexpr int64_t EVAL_TWO_PASS_SLICES = (int64_t)1 << 17;
+
+__global__ void k_invert(const uint32_t* __restrict__ order, int64_t m_pad, uint32_t* __restrict__ pos);
+
 void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t n_obs, const int32_t* const* idx,
               tk_mem mem) {
   ObsSet& o = c->obs;
@@ -71,6 +100,15 @@ void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t 
     o.F32[j].alloc(c, sizeof(float) * (size_t)dims[j] * o.kp[j]);
   }
   o.gl.alloc(c, sizeof(float) * (size_t)std::max<int64_t>(n_obs, 1));
+  o.eval_pos.release();
+  if (eval_on_mfma(o) && n_obs >= EVAL_TWO_PASS && o.plan[eval_mode(o)].L_nz <= EVAL_TWO_PASS_SLICES) {
+    const ModePlan& pl = o.plan[eval_mode(o)];
+    o.eval_pos.alloc(c, sizeof(uint32_t) * (size_t)n_obs);
+    ensure(c, o.gl, sizeof(float) * (size_t)pl.m_pad);
+    hipLaunchKernelGGL(k_invert, dim3(grid_for(pl.m_pad, 256)), dim3(256), 0, c->stream,
+                       pl.order_pad.as<uint32_t>(), pl.m_pad, o.eval_pos.as<uint32_t>());
+    TK_CHECK_LAUNCH();
+  }
   o.Yg.alloc(c, sizeof(float) * (size_t)maxY);
   int64_t pk = 1;
   for (int j = 0; j < N; ++j) pk *= ranks[j];
@@ -157,71 +195,178 @@ __global__ void k_pad_copy(const float* __restrict__ src, int64_t L, int K, floa
 // (a < b the other two modes, G indexed with the first mode fastest).  The
 // observations are walked in the layout of mode c's plan (bins of Lite
 // segments, padded to multiples of four, a segment being one slice's run in
-// one bin).  Per segment the wave forms M once, in the B-operand layout of
-// v_mfma_f32_16x16x4_f32 (lane (q, j) holds M[4q + s][j], s = 0..3, the
-// contraction index of step s being 4q + s); per block of 16 observations
-// four MFMA steps give D = F_a-rows x M with A[i][4q + s] = F_a[l_a(i)][4q + s]
-// (one 16-byte load per lane), and m_i = sum_j D[i][j] F_b[l_b(i)][j] is a sum
-// over the 16 lanes of a row group.  Factors are the 16-float padded copies.
-// Each observation's value goes to its own index (order_pad); padding
-// positions are skipped.
-__global__ __launch_bounds__(256) void k_eval3_slab(const int64_t* __restrict__ bin_pptr,
-                                                    const int32_t* __restrict__ seg_ptr,
-                                                    const int64_t* __restrict__ seg_pbegin,
-                                                    const int32_t* __restrict__ seg_row,
-                                                    const int32_t* __restrict__ row_slice,
-                                                    const int32_t* __restrict__ lay_a, const int32_t* __restrict__ lay_b,
-                                                    const uint32_t* __restrict__ order, const float* __restrict__ Fa,
-                                                    const float* __restrict__ Fb, const float* __restrict__ Fc,
-                                                    const float* __restrict__ G, int Ka, int Kb, int Kc, int sa,
-                                                    int sb, int sc, int64_t P, float* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
-  const int j = lane & 15, q = lane >> 4;
-  const int64_t nw = (int64_t)gridDim.x * 4;
-  for (int64_t bin = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); bin < P; bin += nw) {
-    const int s0 = seg_ptr[bin], s1 = seg_ptr[bin + 1];
-    for (int sg = s0; sg < s1; ++sg) {
-      const int64_t pb = seg_pbegin[sg], pe = seg_pbegin[sg + 1];
-      const int64_t lc = row_slice[seg_row[sg]];
-      // M in the B-operand layout: Mr[s] = M[4q + s][j]
-      float fc[16];
+// one bin).  What bounds it is the gathers of the two factor rows, so a wave
+// takes only EVAL_PART positions of a bin (a small set of observations still
+// fills the chip), keeps three blocks of 16 rows in flight and reads indices three
+// blocks before that.
+//   * M^T is held in the A-operand layout of v_mfma_f32_16x16x4_f32 (lane (q, j)
+//     holds M[4q + s][j] for step s, the contraction index of step s being
+//     4q + s), formed per segment from the core, which a workgroup keeps in LDS
+//     in that layout.
+//   * Four steps with B[4q + s][i] = F_a[l_a(i)][4q + s] (one 16-byte load per
+//     lane) give D[b][i] = (M^T F_a[l_a(i)])[b] in the lane (b / 4, i), which
+//     multiplies it with its own quad of F_b[l_b(i)] (one more 16-byte load) and
+//     adds over the four lane groups.
+// A block ends with its segment; the next one starts there.  Factors are the
+// 16-float padded copies.  Each observation's value goes to its own index
+// (order_pad); padding positions are skipped.
+// 5e7 observations, ranks 16, 500000 x 500000 x 50000, Zipf 1.0: 1.13 ms and the
+// second pass 0.2 (one wave per bin, no row in flight while a block is worked
+// on, four gathers of F_b's entries and scattered writes: 3.33 ms); 2e5
+// observations: 10 us (150 us: 196 waves).
+constexpr int EVAL_PART = 128;
+constexpr int EVAL_WAVES = 8;
+constexpr int EVAL_RING = 3;
+
+struct EvalArgs {
+  const uint32_t* bin_order;   // launch order of the bins (null: as they are)
+  const int64_t* bin_pptr;
+  const int32_t* seg_ptr;
+  const int64_t* seg_pbegin;
+  const int32_t* seg_row;
+  const int32_t* row_slice;
+  const int32_t* lay_a;
+  const int32_t* lay_b;
+  const uint32_t* order;
+  const float* Fa;
+  const float* Fb;
+  const float* Fc;
+  const float* G;
+  int Ka, Kb, Kc, sa, sb, sc;
+  int64_t items;   // bins x parts
+  int parts;       // EVAL_PART-position parts of the longest bin
+};
+
+template <bool SCATTER>
+__global__ __launch_bounds__(64 * EVAL_WAVES) void k_eval3(EvalArgs A, float* __restrict__ out) {
+  __shared__ floatx4_e Gs[16 * 64];   // [c][lane]: G[4q + s][j][c], s = 0..3
+  for (int i = threadIdx.x; i < 16 * 64; i += 64 * EVAL_WAVES) {
+    const int c = i >> 6, j = i & 15, q = (i >> 4) & 3;
+    floatx4_e g;
 #pragma unroll
-      for (int c = 0; c < 16; ++c) fc[c] = Fc[lc * 16 + c];
-      float Mr[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int a = 4 * q + s;
-        float t = 0.f;
-        if (a < Ka && j < Kb)
-          for (int c = 0; c < Kc; ++c) t = fmaf(G[a * sa + j * sb + c * sc], fc[c], t);
-        Mr[s] = t;
+    for (int s = 0; s < 4; ++s) {
+      const int a = 4 * q + s;
+      g[s] = (a < A.Ka && j < A.Kb && c < A.Kc) ? A.G[a * A.sa + j * A.sb + c * A.sc] : 0.f;
+    }
+    Gs[i] = g;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, q = lane >> 4;
+  const int64_t nblk = (A.items + EVAL_WAVES - 1) / EVAL_WAVES;
+  for (int64_t ib = blockIdx.x; ib < nblk; ib += gridDim.x) {
+    const int64_t item = xcd_block(ib, nblk) * EVAL_WAVES + wave;
+    if (item >= A.items) continue;
+    const int64_t place = item / A.parts;
+    const int64_t bin = A.bin_order ? (int64_t)A.bin_order[place] : place;
+    const int64_t b1 = A.bin_pptr[bin + 1];
+    const int64_t p0 = A.bin_pptr[bin] + (item - place * A.parts) * EVAL_PART, p1 = min(p0 + EVAL_PART, b1);
+    if (p0 >= p1) continue;
+    int lo = A.seg_ptr[bin], hi = A.seg_ptr[bin + 1] - 1;   // the segment of p0
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (A.seg_pbegin[mid] <= p0) lo = mid; else hi = mid - 1;
+    }
+    // positions relative to p0 from here on; the lanes' reads stop at the last one
+    const int n = (int)(p1 - p0);
+    const int32_t* la = A.lay_a + p0;
+    const int32_t* lb = A.lay_b + p0;
+    const uint32_t* lo_ = A.order + p0;
+    struct Idx { int pos, end, sg; int a, b; uint32_t o; };   // pos, end, sg are the same in every lane
+    struct Blk { int pos, end, sg; uint32_t o; floatx4_e x, y; };
+    int cpos = 0, csg = lo, cend = (int)min((int64_t)n, A.seg_pbegin[lo + 1] - p0);
+    auto fetch_idx = [&](Idx& r) __attribute__((always_inline)) {
+      r.pos = cpos;
+      r.end = cend;
+      r.sg = csg;
+      const int p = min(cpos + i16, n - 1);
+      r.a = __builtin_nontemporal_load(la + p);
+      r.b = __builtin_nontemporal_load(lb + p);
+      if constexpr (SCATTER) r.o = __builtin_nontemporal_load(lo_ + p);
+      cpos = min(cpos + 16, cend);
+      if (cpos == cend && cend < n) {
+        ++csg;
+        cend = (int)min((int64_t)n, A.seg_pbegin[csg + 1] - p0);
       }
-      for (int64_t p0 = pb; p0 < pe; p0 += 16) {
-        const int64_t pi = p0 + j;   // this lane's observation for the A operand
-        const bool ok = pi < pe;
-        const int la = ok ? lay_a[pi] : 0;
-        const floatx4_e xa = ok ? *reinterpret_cast<const floatx4_e*>(Fa + (int64_t)la * 16 + 4 * q)
-                                : floatx4_e{0.f, 0.f, 0.f, 0.f};
-        floatx4_e D = {0.f, 0.f, 0.f, 0.f};
+    };
+    auto fetch = [&](const Idx& i, Blk& r) __attribute__((always_inline)) {
+      r.pos = i.pos;
+      r.end = i.end;
+      r.sg = i.sg;
+      if constexpr (SCATTER) r.o = i.o;
+      r.x = *reinterpret_cast<const floatx4_e*>(A.Fa + (int64_t)i.a * 16 + 4 * q);
+      r.y = *reinterpret_cast<const floatx4_e*>(A.Fb + (int64_t)i.b * 16 + 4 * q);
+    };
+    floatx4_e M = {0.f, 0.f, 0.f, 0.f};
+    int msg = -1;
+    auto consume = [&](const Blk& r) __attribute__((always_inline)) {
+      if (r.pos >= r.end) return;
+      if (r.sg != msg) {   // a new segment: its M
+        msg = r.sg;
+        const float* fc = A.Fc + (int64_t)A.row_slice[A.seg_row[msg]] * 16;
+        M = floatx4_e{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < A.Kc; ++c) M += Gs[64 * c + lane] * fc[c];
+      }
+      floatx4_e D = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) D = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[s], Mr[s], D, 0, 0, 0);
-        // D[4q + r][j] in register r: times F_b[l_b(obs 4q + r)][j], summed over the row group
+      for (int s = 0; s < 4; ++s) D = __builtin_amdgcn_mfma_f32_16x16x4f32(M[s], r.x[s], D, 0, 0, 0);
+      float w = D[0] * r.y[0];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t pr = p0 + 4 * q + r;
-          const bool okr = pr < pe;
-          const float v = okr ? D[r] * Fb[(int64_t)lay_b[pr] * 16 + j] : 0.f;
-          float w = v;
-#pragma unroll
-          for (int x = 8; x >= 1; x >>= 1) w += __shfl_xor(w, x, 16);
-          if (j == 0 && okr) {
-            const uint32_t e = order[pr];
-            if (e != 0xffffffffu) out[e] = w;
-          }
+      for (int s = 1; s < 4; ++s) w = fmaf(D[s], r.y[s], w);
+      w += __shfl_xor(w, 16, 64);
+      w += __shfl_xor(w, 32, 64);
+      if (q == 0 && r.pos + i16 < r.end) {
+        if constexpr (SCATTER) {
+          if (r.o != 0xffffffffu) out[r.o] = w;
+        } else {
+          __builtin_nontemporal_store(w, out + p0 + r.pos + i16);   // padding positions too: never read
         }
+      }
+    };
+    Idx ix[EVAL_RING];
+    Blk ring[EVAL_RING];
+#pragma unroll
+    for (int d = 0; d < EVAL_RING; ++d) fetch_idx(ix[d]);
+#pragma unroll
+    for (int d = 0; d < EVAL_RING; ++d) {
+      fetch(ix[d], ring[d]);
+      fetch_idx(ix[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    while (ring[0].pos < ring[0].end) {
+#pragma unroll
+      for (int d = 0; d < EVAL_RING; ++d) {
+        consume(ring[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(ix[d], ring[d]);
+        fetch_idx(ix[d]);
       }
     }
   }
+}
+
+// pos[e] = layout position of observation e (the inverse of order_pad)
+__global__ void k_invert(const uint32_t* __restrict__ order, int64_t m_pad, uint32_t* __restrict__ pos) {
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < m_pad; p += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t e = order[p];
+    if (e != 0xffffffffu) pos[e] = (uint32_t)p;
+  }
+}
+
+// out[e] = lay[pos[e]].  Each XCD takes a contiguous range of e.
+constexpr int TAKE_PER = 8;   // values per thread, 256 apart
+__global__ __launch_bounds__(256) void k_take(const float* __restrict__ lay, const uint32_t* __restrict__ pos, int64_t n,
+                                              float* __restrict__ out) {
+  const int64_t e0 = xcd_block(blockIdx.x, gridDim.x) * (256 * TAKE_PER) + threadIdx.x;
+  uint32_t p[TAKE_PER];
+#pragma unroll
+  for (int i = 0; i < TAKE_PER; ++i) p[i] = e0 + 256 * i < n ? __builtin_nontemporal_load(pos + e0 + 256 * i) : 0;
+  float v[TAKE_PER];
+#pragma unroll
+  for (int i = 0; i < TAKE_PER; ++i) v[i] = e0 + 256 * i < n ? lay[p[i]] : 0.f;
+#pragma unroll
+  for (int i = 0; i < TAKE_PER; ++i)
+    if (e0 + 256 * i < n) __builtin_nontemporal_store(v[i], out + e0 + 256 * i);
 }
 
 static const float* dev_copy_f32(Ctx* c, Buf& tmp, const float* src, size_t n, tk_mem mem) {
@@ -249,11 +394,9 @@ void obs_eval(Ctx* c, const float* core, const float* const* F, float* model, tk
     tOut.alloc(c, sizeof(float) * (size_t)std::max<int64_t>(o.n_obs, 1));
     out = tOut.as<float>();
   }
-  if (o.n_obs > 0 && N == 3 && o.K[0] <= 16 && o.K[1] <= 16 && o.K[2] <= 16) {
+  if (o.n_obs > 0 && eval_on_mfma(o)) {
     // group by the mode with the fewest nonempty slices; factors as 16-float rows
-    int mc = 0;
-    for (int jn = 1; jn < 3; ++jn)
-      if (o.plan[jn].L_nz < o.plan[mc].L_nz) mc = jn;
+    const int mc = eval_mode(o);
     const int ma = mc == 0 ? 1 : 0, mb = mc == 2 ? 1 : 2;
     for (int jn = 0; jn < 3; ++jn) {
       hipLaunchKernelGGL(k_pad_copy, dim3(grid_for(o.dims[jn] * 16, 256)), dim3(256), 0, c->stream, fp.p[jn],
@@ -262,12 +405,35 @@ void obs_eval(Ctx* c, const float* core, const float* const* F, float* model, tk
     }
     const int st[3] = {1, o.K[0], o.K[0] * o.K[1]};
     const ModePlan& pl = o.plan[mc];
-    hipLaunchKernelGGL(k_eval3_slab, dim3(grid_for(pl.P, 4, 16384)), dim3(256), 0, c->stream,
-                       pl.bin_pptr.as<int64_t>(), pl.seg_ptr.as<int32_t>(), pl.seg_pbegin.as<int64_t>(),
-                       pl.seg_row.as<int32_t>(), pl.row_slice.as<int32_t>(), pl.lay_idx[0].as<int32_t>(),
-                       pl.lay_idx[1].as<int32_t>(), pl.order_pad.as<uint32_t>(), o.F32[ma].as<float>(),
-                       o.F32[mb].as<float>(), o.F32[mc].as<float>(), G, o.K[ma], o.K[mb], o.K[mc], st[ma], st[mb],
-                       st[mc], pl.P, out);
+    EvalArgs a{};
+    a.bin_order = pl.bin_order.as<uint32_t>();
+    a.bin_pptr = pl.bin_pptr.as<int64_t>();
+    a.seg_ptr = pl.seg_ptr.as<int32_t>();
+    a.seg_pbegin = pl.seg_pbegin.as<int64_t>();
+    a.seg_row = pl.seg_row.as<int32_t>();
+    a.row_slice = pl.row_slice.as<int32_t>();
+    a.lay_a = pl.lay_idx[0].as<int32_t>();
+    a.lay_b = pl.lay_idx[1].as<int32_t>();
+    a.order = pl.order_pad.as<uint32_t>();
+    a.Fa = o.F32[ma].as<float>();
+    a.Fb = o.F32[mb].as<float>();
+    a.Fc = o.F32[mc].as<float>();
+    a.G = G;
+    a.Ka = o.K[ma]; a.Kb = o.K[mb]; a.Kc = o.K[mc];
+    a.sa = st[ma]; a.sb = st[mb]; a.sc = st[mc];
+    a.parts = (int)std::max<int64_t>(1, ceil_div(pl.E_pad_max, EVAL_PART));
+    a.items = pl.P * a.parts;
+    // workgroups stay for several items (the core is laid out once): three per
+    // compute unit run at a time
+    const dim3 g(grid_for(a.items, EVAL_WAVES, 8 * (int64_t)c->cu_count)), b(64 * EVAL_WAVES);
+    if (o.eval_pos) {
+      hipLaunchKernelGGL(k_eval3<false>, g, b, 0, c->stream, a, o.gl.as<float>());
+      TK_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_take, dim3((unsigned)ceil_div(o.n_obs, 256 * TAKE_PER)), dim3(256), 0, c->stream,
+                         o.gl.as<float>(), o.eval_pos.as<uint32_t>(), o.n_obs, out);
+    } else {
+      hipLaunchKernelGGL(k_eval3<true>, g, b, 0, c->stream, a, out);
+    }
     TK_CHECK_LAUNCH();
   } else if (o.n_obs > 0) {
     const int use_lds = (size_t)pK * 4 <= std::min<size_t>(c->lds_per_block, 65536) ? 1 : 0;

@@ -365,13 +365,13 @@ __global__ void k_coarse_bins(const int64_t* __restrict__ seg_bin, const int64_t
 // shared piece keeps its place among the P bins.
 __global__ void k_bin_order_key(const int32_t* __restrict__ seg_ptr, const int64_t* __restrict__ seg_begin,
                                 const int64_t* __restrict__ seg_pbegin, const int32_t* __restrict__ seg_slot,
-                                const int32_t* __restrict__ lay, int64_t P, int64_t L, uint32_t* __restrict__ key,
+                                const uint32_t* __restrict__ lay, int64_t P, int64_t L, uint32_t* __restrict__ key,
                                 uint32_t* __restrict__ val) {
   for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < P; p += (int64_t)gridDim.x * blockDim.x) {
     uint32_t k = (uint32_t)(p * L / P);
     const int32_t s = seg_ptr[p + 1] - 1;
     if (s >= seg_ptr[p] && seg_slot[s] >= 0)   // padding elements come last: the middle is a real one
-      k = (uint32_t)lay[seg_pbegin[s] + (seg_begin[s + 1] - seg_begin[s] - 1) / 2];
+      k = lay[seg_pbegin[s] + (seg_begin[s + 1] - seg_begin[s] - 1) / 2];
     key[p] = k;
     val[p] = (uint32_t)p;
   }
@@ -681,18 +681,23 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   // 2e6, 2e8 draws: 26 pieces 2.41 -> 1.83 ms, 108 pieces 2.19 -> 1.45 ms, L2
   // misses halved); with fewer the ranges are wide (3.8 to 5.8 pieces: between
   // 1% faster and 2% slower).  Below about 4096 bins all of them run at once.
-  // Four modes are bound by the matrix cores (no change either way), and
-  // observations, which come in no order, have no ranges.
-  if (N == 3 && vals && P >= 4096 && pl.n_slots >= 8 * nbad) {
-    const int64_t La = dims[n == 0 ? 1 : 0];
+  // Four modes are bound by the matrix cores (no change either way).
+  // Observations stay in input order inside a slice, so their pieces cover ranges
+  // of the observations themselves: the residuals (adjoint) and results (forward)
+  // of a range then stay in L2 (5e7 observations, Zipf 1.0, 16 pieces a slice and
+  // more: adjoint 5.87 -> 5.17 ms; ordering each slice by its widest other mode
+  // instead gave 5.68 and took 30% longer to load).
+  if (N == 3 && P >= 4096 && pl.n_slots >= 8 * nbad) {
+    const int64_t range = vals ? dims[n == 0 ? 1 : 0] : m;
     Buf bk(c, 4 * (size_t)P), bk2(c, 4 * (size_t)P), bv(c, 4 * (size_t)P);
     pl.bin_order.alloc(c, 4 * (size_t)P);
     hipLaunchKernelGGL(k_bin_order_key, dim3(grid_for(P, B)), dim3(B), 0, c->stream, pl.seg_ptr.as<int32_t>(),
                        pl.seg_begin.as<int64_t>(), pl.seg_pbegin.as<int64_t>(), pl.seg_slot.as<int32_t>(),
-                       pl.lay_idx[0].as<int32_t>(), P, La, bk.as<uint32_t>(), bv.as<uint32_t>());
+                       vals ? pl.lay_idx[0].as<uint32_t>() : pl.order_pad.as<uint32_t>(), P, range,
+                       bk.as<uint32_t>(), bv.as<uint32_t>());
     TK_CHECK_LAUNCH();
     sort_pairs_u32(c, bk.as<uint32_t>(), bk2.as<uint32_t>(), bv.as<uint32_t>(), pl.bin_order.as<uint32_t>(), P,
-                   bits_for_len(La));
+                   bits_for_len(range));
   }
   c->sync();
   pl.row_of = std::move(row_of);
