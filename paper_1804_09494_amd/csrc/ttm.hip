@@ -9,7 +9,8 @@
 // several bins go to a partial slot, which the fixup kernels sum in bin order.
 // Four kernels:
 //   * k_ttm3_mfma: three modes, other ranks <= 16, on the matrix cores;
-//   * k_ttm3w_mfma: three modes, other ranks <= 32, one above 16, likewise;
+//   * k_ttm3w_mfma: three modes, other ranks <= 32, one above 16, likewise, and
+//     smaller ranks where there are few bins;
 //   * k_ttm4_mfma: four modes, other ranks <= 16, on the matrix cores;
 //   * k_ttm_cols:  every other shape, on the vector ALUs.
 // None of them uses atomics: every sum runs in a fixed order.
@@ -440,9 +441,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
   }
 }
 
-// ---- three-mode TTM-chain with wide factors on the matrix cores ---------------------------------
+// ---- three-mode TTM-chain with wide factors, or few bins, on the matrix cores -------------------
 //
-// Three modes, both remaining ranks at most 32 and one of them above 16.
+// Three modes, both remaining ranks at most 32 and one of them above 16; or both
+// at most 16 and too few bins for one wave each to fill the chip
+// (TTM3_FEW_BINS; GATHER: the values come through A.val_order, as in k_ttm3_mfma).
 // Y[row] as K_a x K_b is the same sum of (val F_a)^T F_b as above, covered by
 // TA x TB MFMA tiles (ceil(K_a / 16), ceil(K_b / 16)).  What bounds it is the
 // matrix cores (512 cycles per 16 elements with 2 x 2 tiles), so a few waves per
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
 // launch against 0.10 ms of matrix-core time.
 constexpr int TTM3W_WAVES = 8;
 
-template <int TA, int TB>
+template <int TA, int TB, bool GATHER = false>
 __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int nseg_pad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int ka = A.Kj[0], kb = A.Kj[1], khat = A.khat;
@@ -563,11 +566,11 @@ __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int 
     // block g: lane l takes element g + l/4 and quad l%4 of every plane.
     // Reads past the wave's part are clamped to its last element (their
     // steps are not run; a step never ends inside a quad of elements).
-    struct Idx { int a, b; float v; };
+    struct Idx { int a, b; uint32_t v; };   // v: the value, or (GATHER) where it is
     struct Blk { u32x4 x[TA], y[TB]; float v; };
     const int* la = A.lay[0] + e0;
     const int* lb = A.lay[1] + e0;
-    const float* lv = A.val + e0;
+    const uint32_t* lv = (GATHER ? A.val_order : reinterpret_cast<const uint32_t*>(A.val)) + e0;
     int oa[TA], ob[TB];
 #pragma unroll
     for (int t = 0; t < TA; ++t) oa[t] = min(16 * t + 4 * (lane & 3), A.fstride[0] - 4);
@@ -582,7 +585,12 @@ __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int 
     auto fetch = [&](const Idx& i, Blk& r) __attribute__((always_inline)) {
       const float* pa = A.F[0] + (int64_t)i.a * A.fstride[0];
       const float* pb = A.F[1] + (int64_t)i.b * A.fstride[1];
-      r.v = i.v;
+      if constexpr (GATHER) {
+        const float x = A.val[i.v == ~0u ? 0u : i.v];   // padding (~0) is zero
+        r.v = i.v == ~0u ? 0.f : x;
+      } else {
+        r.v = __uint_as_float(i.v);
+      }
 #pragma unroll
       for (int t = 0; t < TA; ++t) r.x[t] = *reinterpret_cast<const u32x4*>(pa + oa[t]);
 #pragma unroll
@@ -1095,6 +1103,36 @@ int ttm_rows_cap(Ctx* c, int64_t tile_w) {
   return (int)cap;
 }
 
+// Below this many bins (three quarters of the SIMDs) the one-wave kernel leaves SIMDs idle and
+// its time is one bin's chain of blocks; up to eight waves then share a bin.
+// Three modes with their fixup at ranks 10: 45 bins 47 -> 34 us, 224 bins 49 ->
+// 37, 670 bins 52 -> 46, 1340 bins 60 -> 61, 2233 bins 75 -> 84.  BF16 tiles stay
+// with the one-wave kernel.
+constexpr int64_t TTM3_FEW_BINS = 768;
+
+static void ttm3w_launch(Ctx* c, const ModePlan& pl, const TtmArgs& a) {
+  // waves per bin: at least 64 elements (four blocks) each
+  int nw = TTM3W_WAVES;
+  while (nw > 1 && 64 * nw > pl.E_pad_max) nw >>= 1;
+  const int TA = a.Kj[0] > 16 ? 2 : 1, TB = a.Kj[1] > 16 ? 2 : 1;
+  const int nseg_pad = (int)((pl.R_max + 3) & ~(int64_t)3);
+  const size_t lds = 3 * sizeof(int) * (size_t)nseg_pad +
+                     sizeof(float) * (size_t)nw * (256 * (size_t)(TA + TB) + (size_t)pl.khat);
+  TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
+  const dim3 g((unsigned)pl.P), b(64 * nw);
+  if (TA == 2 && TB == 2)
+    hipLaunchKernelGGL((k_ttm3w_mfma<2, 2>), g, b, lds, c->stream, a, nseg_pad);
+  else if (TA == 2)
+    hipLaunchKernelGGL((k_ttm3w_mfma<2, 1>), g, b, lds, c->stream, a, nseg_pad);
+  else if (TB == 2)
+    hipLaunchKernelGGL((k_ttm3w_mfma<1, 2>), g, b, lds, c->stream, a, nseg_pad);
+  else if (a.val_order)
+    hipLaunchKernelGGL((k_ttm3w_mfma<1, 1, true>), g, b, lds, c->stream, a, nseg_pad);
+  else
+    hipLaunchKernelGGL((k_ttm3w_mfma<1, 1>), g, b, lds, c->stream, a, nseg_pad);
+  TK_CHECK_LAUNCH();
+}
+
 // TTM-chain of the elements of plan `pl` along mode n with FP32 factor copies
 // F32[j] (row stride kp[j]) of every mode j != n; values are the plan's layout values.
 void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const float* const* F32, const int* kp,
@@ -1144,6 +1182,8 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
              "TTM-chain: gathered values need the three-mode matrix-core kernel");
   if (!pl.whole_slices && c->opt.ttm_kernel == TK_TTM_FIBER && ttm_uses_fiber(N, K, n, kp)) {
     ttm_fiber_launch(c, pl, a, N);
+  } else if (!vector_only && !bf16 && ttm_uses_mfma(N, K, n, kp) && pl.P < TTM3_FEW_BINS) {
+    ttm3w_launch(c, pl, a);
   } else if (!vector_only && ttm_uses_mfma(N, K, n, kp)) {
     const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
     const size_t lds = 12 * (size_t)Epad + sizeof(float) * 512 + sizeof(float) * (size_t)pl.R_max * (size_t)pl.khat;
@@ -1158,22 +1198,7 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
     }
     TK_CHECK_LAUNCH();
   } else if (!vector_only && ttm_uses_mfma3w(N, K, n, kp)) {
-    // waves per bin: at least 256 elements each
-    int nw = TTM3W_WAVES;
-    while (nw > 1 && 256 * nw > pl.E_pad_max) nw >>= 1;
-    const int TA = a.Kj[0] > 16 ? 2 : 1, TB = a.Kj[1] > 16 ? 2 : 1;
-    const int nseg_pad = (int)((pl.R_max + 3) & ~(int64_t)3);
-    const size_t lds = 3 * sizeof(int) * (size_t)nseg_pad +
-                       sizeof(float) * (size_t)nw * (256 * (size_t)(TA + TB) + (size_t)pl.khat);
-    TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
-    const dim3 g((unsigned)pl.P), b(64 * nw);
-    if (TA == 2 && TB == 2)
-      hipLaunchKernelGGL((k_ttm3w_mfma<2, 2>), g, b, lds, c->stream, a, nseg_pad);
-    else if (TA == 2)
-      hipLaunchKernelGGL((k_ttm3w_mfma<2, 1>), g, b, lds, c->stream, a, nseg_pad);
-    else
-      hipLaunchKernelGGL((k_ttm3w_mfma<1, 2>), g, b, lds, c->stream, a, nseg_pad);
-    TK_CHECK_LAUNCH();
+    ttm3w_launch(c, pl, a);
   } else if (!vector_only && ttm_uses_mfma4(N, K, n, kp)) {
     const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
     const int nseg_pad = (int)((pl.R_max + 3) & ~(int64_t)3);
