@@ -31,6 +31,8 @@
 // 96 columns either way.
 // The tall-skinny products are plain FP64 kernels with fixed-order partial sums.
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 
@@ -75,18 +77,16 @@ __global__ __launch_bounds__(NW * 64) void k_kr_nn(const TA* __restrict__ A, int
     const double b = (kk < k1 && i16 < nc) ? C[(int64_t)kk * ldc + i16] : 0.0;
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
   }
-  // the waves' partials, summed by wave 0 in wave order
+  // the waves' partials, summed in wave order (wave r sums register r)
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave * 256 + r * 64 + lane] = acc[r];
   __syncthreads();
-  if (wave == 0 && i16 < nc) {
+  if (wave < 4 && i16 < nc) {
+    double t = 0.0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double t = 0.0;
-      for (int w = 0; w < NW; ++w) t += red[w * 256 + r * 64 + lane];
-      const int64_t rr = r0 + q + 4 * r;
-      if (rr < n) D[rr * ldd + i16] = SUB ? S[rr * lds + i16] - t : t;
-    }
+    for (int w = 0; w < NW; ++w) t += red[w * 256 + wave * 64 + lane];
+    const int64_t rr = r0 + q + 4 * wave;
+    if (rr < n) D[rr * ldd + i16] = SUB ? S[rr * lds + i16] - t : t;
   }
 }
 
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(KR_TN_WAVES * 64) void k_kr_tn(const TA* __restrict
   const int64_t s0 = z0 + wave * nw, s1 = min(s0 + nw, z1);
   const bool aok = i0 + i16 < J, bok = c0 + i16 < nc;
   doublex4_k acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
+#pragma unroll 16
   for (int64_t r = s0; r < s1; r += 4) {
     const int64_t rr = r + q;
     const bool rok = rr < s1;
@@ -117,19 +117,17 @@ __global__ __launch_bounds__(KR_TN_WAVES * 64) void k_kr_tn(const TA* __restrict
     const double b = (rok && bok) ? B[rr * ldb + c0 + i16] : 0.0;
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
   }
-  // the waves' partials, summed by wave 0 in wave order
+  // the waves' partials, summed in wave order
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave * 256 + r * 64 + lane] = acc[r];
   __syncthreads();
-  if (wave == 0 && bok) {
+  if (wave < 4 && bok) {   // wave r sums the waves' register r
     double* out = part + (int64_t)blockIdx.z * J * nc;
+    double t = 0.0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double t = 0.0;
-      for (int w = 0; w < KR_TN_WAVES; ++w) t += red[w * 256 + r * 64 + lane];
-      const int ii = i0 + q + 4 * r;
-      if (ii < J) out[(int64_t)ii * nc + c0 + i16] = t;
-    }
+    for (int w = 0; w < KR_TN_WAVES; ++w) t += red[w * 256 + wave * 64 + lane];
+    const int ii = i0 + q + 4 * wave;
+    if (ii < J) out[(int64_t)ii * nc + c0 + i16] = t;
   }
 }
 
@@ -256,6 +254,161 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
   }
 }
 
+// Q[:, 0..15] (n x 16, ldq) = orthonormal basis of W (n x 16) in one workgroup:
+// the three passes of shifted CholeskyQR3 that k_kr_tn, k_kr_chol and k_kr_nn
+// make in nine launches, with W in registers from the first to the last.
+// What bounds those is a launch and a trip through memory for every step of a
+// 16 x 16 problem.  Wave w holds TPW 16-row tiles of W, register s of a tile
+// W[4s + q][j] in lane (q, j), which is both operands of the Gram's
+// v_mfma_f64_16x16x4_f64.  The waves' Grams are summed in LDS in wave order; one
+// more wave factorises, its rows of 16 lanes all alike (lane k of a row holds
+// column k, and another column's entry is one 64-bit row broadcast); the
+// product with R^-1 takes the tile through LDS into row-major operand order and
+// leaves it as it was held.  Measured at n = 1000: 83 us of kernels and nine
+// launches -> 24 us and one (12 us at n = 216, 47 us at n = 1900).
+template <int I>
+__device__ __forceinline__ double kr_bcast(double x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x150 + I, 0xf, 0xf, true);
+}
+template <int... I, class F>
+__device__ __forceinline__ void kr_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void kr_for(F&& f) {
+  kr_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+constexpr int KR_QR_WAVES = 8;   // waves holding rows; one more factorises
+constexpr int KR_QR_TS = 17;     // row stride of a tile in LDS
+
+template <int TPW>
+__global__ __launch_bounds__(64 * (KR_QR_WAVES + 1)) void k_kr_cholqr3(const double* __restrict__ W,
+                                                                      double* __restrict__ Q, int ldq, int n) {
+  __shared__ double part[KR_QR_WAVES * 16 * KR_QR_TS];   // the waves' Grams; a tile per wave
+  __shared__ double gm[256], ri[256];
+  const int lane = threadIdx.x & 63, j = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave == KR_QR_WAVES) {
+    // The factorising wave: as k_kr_chol, on a wave of its own
+    // (beside the rows its registers would spill).  Four barriers per pass, as below.
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+      __syncthreads();
+      __syncthreads();
+      double x[16], z[16];   // column j of the Gram and of the identity
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = gm[i * 16 + j];
+      double dmax = 0.0, tr = 0.0;
+      kr_for<16>([&](auto ii) __attribute__((always_inline)) {
+        constexpr int i = decltype(ii)::value;
+        tr += kr_bcast<i>(x[i]);
+      });
+      const double sh = pass == 0 ? 11.0 * ((double)n * 16 + 16.0 * 17) * 0x1p-53 * tr : 0.0;
+      int jj = j;
+      asm volatile("" : "+v"(jj));   // compared here: the sixteen masks kept over the passes spill
+      kr_for<16>([&](auto ii) __attribute__((always_inline)) {
+        constexpr int i = decltype(ii)::value;
+        x[i] += jj == i ? sh : 0.0;
+        z[i] = jj == i ? 1.0 : 0.0;
+        dmax = fmax(dmax, kr_bcast<i>(x[i]));
+      });
+      // R in the upper triangle: lane k holds R[i][k] in x[i], k >= i (entries
+      // below it are not read).  The same row operations on the identity leave
+      // column j of R^-T in z, with the factorisation's own broadcasts.
+      kr_for<16>([&](auto cc) __attribute__((always_inline)) {
+        constexpr int c = decltype(cc)::value;
+        const double d = kr_bcast<c>(x[c]);
+        const bool ok = d > 1e-14 * dmax;   // a dependent column is dropped
+        const double dd = ok ? d : 1.0;
+        double y = __builtin_amdgcn_rsq(dd);   // 1 / sqrt, refined twice
+        double e = fma(-dd * y, y, 1.0);
+        y = fma(0.5 * y, e, y);
+        e = fma(-dd * y, y, 1.0);
+        y = fma(0.5 * y, e, y);
+        y = ok ? y : 0.0;
+        x[c] *= y;
+        z[c] *= y;
+        kr_for<15 - c>([&](auto ii) __attribute__((always_inline)) {
+          constexpr int i = decltype(ii)::value + c + 1;
+          const double r = -kr_bcast<i>(x[c]);
+          x[i] = fma(r, x[c], x[i]);
+          z[i] = fma(r, z[c], z[i]);
+        });
+      });
+      if (!(dmax > 0.0)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.0;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ri[j * 16 + i] = z[i];   // the four rows of lanes alike
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
+  double* mine = part + wave * 16 * KR_QR_TS;
+  doublex4_k w[TPW];
+  // all loads at once: rows past n read the last one and count as zero
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w[t][s] = W[(int64_t)min(16 * (wave * TPW + t) + 4 * s + q, n - 1) * 16 + j];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (16 * (wave * TPW + t) + 4 * s + q >= n) w[t][s] = 0.0;
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    doublex4_k g[4] = {};   // independent chains
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) g[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[t][s], w[t][s], g[s], 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mine[(q + 4 * r) * 16 + j] = (g[0][r] + g[1][r]) + (g[2][r] + g[3][r]);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      double t = 0.0;
+#pragma unroll
+      for (int v = 0; v < KR_QR_WAVES; ++v) t += part[v * 16 * KR_QR_TS + threadIdx.x];
+      gm[threadIdx.x] = t;
+    }
+    __syncthreads();
+    // the factorising wave's turn
+    __syncthreads();
+    double b[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) b[s] = ri[(4 * s + q) * 16 + j];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) mine[(4 * s + q) * KR_QR_TS + j] = w[t][s];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      doublex4_k d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(mine[j * KR_QR_TS + 4 * s + q], b[s], d, 0, 0, 0);
+      w[t] = d;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();   // the tiles' places become the Grams' again
+  }
+  asm volatile("" : "+s"(ldq));   // the addresses are formed here, not before the passes
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int r = 16 * (wave * TPW + t) + 4 * s + q;
+      if (r < n) Q[(int64_t)r * ldq + j] = w[t][s];
+    }
+}
+
 // Start block (n x B): columns 0..kw-1 from the warm vectors (n x kw,
 // row-major), the rest seeded directions (SplitMix64 of (column, row),
 // uniform in [-1, 1)).
@@ -335,6 +488,24 @@ void nn(Ctx* c, const TA* A, int64_t lda, int J, const double* C, int ldc, const
 // alternating, the last one written into Q)
 template <int B>
 void cholqr(Ctx* c, const KrBufs& b, int n, int q0) {
+  if constexpr (B == 16) {
+    // one workgroup holds up to 2048 rows in registers
+    const int tiles = (int)ceil_div(n, 16 * KR_QR_WAVES);
+    const dim3 g(1), t(64 * (KR_QR_WAVES + 1));
+    double* Q = b.Q + q0;
+    if (tiles <= 16) {
+      if (tiles <= 2)
+        hipLaunchKernelGGL(k_kr_cholqr3<2>, g, t, 0, c->stream, b.W, Q, KR_M, n);
+      else if (tiles <= 4)
+        hipLaunchKernelGGL(k_kr_cholqr3<4>, g, t, 0, c->stream, b.W, Q, KR_M, n);
+      else if (tiles <= 8)
+        hipLaunchKernelGGL(k_kr_cholqr3<8>, g, t, 0, c->stream, b.W, Q, KR_M, n);
+      else
+        hipLaunchKernelGGL(k_kr_cholqr3<16>, g, t, 0, c->stream, b.W, Q, KR_M, n);
+      TK_CHECK_LAUNCH();
+      return;
+    }
+  }
   double* A = b.small;            // B x B Gram
   double* Ri = b.small + B * B;
   double* src = b.W;
