@@ -14,8 +14,7 @@
 
 namespace tk {
 
-int uw_product(Ctx* c, const float* Y, int64_t R, int khat, const double* W, int K, double* U, double* part);
-int uw_product_parts(int64_t R);
+void uw_rows(Ctx* c, const float* Y, int64_t R, int khat, const double* W, int K, const int32_t* row_slice, float* dF);
 
 __global__ void k_obs_validate(const int32_t* __restrict__ idx, int64_t m, int64_t L, int32_t* __restrict__ flag) {
   int bad = 0;
@@ -522,16 +521,6 @@ __global__ void k_core_unfold_t(const float* __restrict__ G, int N, const int32_
   }
 }
 
-// dF rows from U = Y^g W (R x K, FP64): dF[row_slice[r]] = U[r], FP32.
-__global__ void k_scatter_rows(const double* __restrict__ U, int64_t R, int K, const int32_t* __restrict__ row_slice,
-                               float* __restrict__ dF) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < R * K; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / K;
-    const int k = (int)(i - r * K);
-    dF[(int64_t)row_slice[r] * K + k] = (float)U[i];
-  }
-}
-
 // dcore[c0 + K0 * col] = sum_r F0[slice(r)][c0] * Yg[r][col] (the general path, K_0 above 16).
 __global__ __launch_bounds__(256) void k_dcore(const float* __restrict__ Yg, int64_t R, int khat,
                                                const float* __restrict__ F0, int K0, int kp0,
@@ -642,18 +631,14 @@ void obs_adjoint(Ctx* c, const float* g, const float* core, const float* const* 
       TK_CHECK_LAUNCH();
     }
     if (pl.L_nz > 0 && o.K[n] <= 16) {
-      // dF_n = Y^g_(n) G_(n)^T on the matrix cores, then scattered to the slices' rows
+      // dF_n = Y^g_(n) G_(n)^T on the matrix cores, written to the slices' rows
       const int Kn = o.K[n];
-      ensure(c, c->small64, sizeof(double) * ((size_t)khat * Kn + (size_t)uw_product_parts(pl.L_nz) * Kn * Kn));
-      ensure(c, c->U64, sizeof(double) * (size_t)pl.L_nz * Kn);
+      ensure(c, c->small64, sizeof(double) * (size_t)khat * Kn);
       double* W = c->small64.as<double>();
       hipLaunchKernelGGL(k_core_unfold_t, dim3(grid_for((int64_t)khat * Kn, 256, 256)), dim3(256), 0, c->stream, G, N,
                          o.Kd.as<int32_t>(), n, khat, W);
       TK_CHECK_LAUNCH();
-      uw_product(c, Yg, pl.L_nz, khat, W, Kn, c->U64.as<double>(), W + (size_t)khat * Kn);
-      hipLaunchKernelGGL(k_scatter_rows, dim3(grid_for(pl.L_nz * Kn, 256)), dim3(256), 0, c->stream,
-                         c->U64.as<double>(), pl.L_nz, Kn, pl.row_slice.as<int32_t>(), dFn);
-      TK_CHECK_LAUNCH();
+      uw_rows(c, Yg, pl.L_nz, khat, W, Kn, pl.row_slice.as<int32_t>(), dFn);
     } else if (pl.L_nz > 0) {
       const size_t lds = sizeof(float) * (size_t)o.K[n] * khat;
       TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "adjoint: K_n x Khat too large for LDS");

@@ -26,6 +26,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace tk {
 
@@ -533,12 +534,6 @@ static SmallLayout small_layout(int n) {
   return L;
 }
 
-// x of lane N of this lane's row of 16 (one 64-bit move)
-template <int N>
-__device__ __forceinline__ double row_bcast(double x) {
-  return __builtin_amdgcn_mov_dpp(x, 0x150 + N, 0xf, 0xf, true);
-}
-
 // Newton-refined hardware reciprocal
 __device__ __forceinline__ double rcp2(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -551,16 +546,6 @@ template <int NC>
 __device__ __forceinline__ double col_of(const double (&x)[NC], int J) {
   const double a = rl(x[0], J & 63), b = rl(x[NC - 1], J & 63);   // both read: a select of two registers
   return J < 64 ? a : b;                                          // by index would put them in memory
-}
-
-// Calls f(integral constant 0 .. N-1).
-template <int... I, class F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
 // NG: 16-row groups of the matrix (n <= 16 NG).

@@ -35,6 +35,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace tk {
 
@@ -169,13 +170,6 @@ __global__ __launch_bounds__(256) void k_colsq_part(const float* __restrict__ Y,
 // its row of R is set to e_j and its column of Rinv to zero, so it adds
 // nothing to the other columns and comes out zero.  An all-zero block zeroes
 // Rinv.
-// x of lane l (l wave-uniform)
-__device__ __forceinline__ double kr_lane(double x, int l) {
-  const long long v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)(unsigned)(v & 0xffffffffLL), l);
-  const int hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 
 // Lane k keeps column k of the block in registers (x[i] = A[i][k], then
 // R[i][k] in the upper triangle); an entry of another column is read across
@@ -191,7 +185,7 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
     double tr = 0.0;
 #pragma unroll
     for (int i = 0; i < B; ++i)
-      if (i < b) tr += kr_lane(x[i], i);
+      if (i < b) tr += lane_value(x[i], i);
     const double sh = 11.0 * ((double)shift_rows * b + (double)b * (b + 1)) * 0x1p-53 * tr;
 #pragma unroll
     for (int i = 0; i < B; ++i)
@@ -200,7 +194,7 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
   double dmax = 0.0;
 #pragma unroll
   for (int i = 0; i < B; ++i)
-    if (i < b) dmax = fmax(dmax, kr_lane(x[i], i));
+    if (i < b) dmax = fmax(dmax, lane_value(x[i], i));
   if (!(dmax > 0.0)) {
     for (int i = l; i < b * b; i += 64) Rinv[i] = 0.0;
     return;
@@ -210,7 +204,7 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
 #pragma unroll
   for (int j = 0; j < B; ++j) {
     if (j < b) {
-      const double d = kr_lane(x[j], j);
+      const double d = lane_value(x[j], j);
       if (!(d > 1e-14 * dmax)) {   // dependent column: dropped
         dead |= 1ull << j;
         if (l == j) x[j] = 1.0;
@@ -223,7 +217,7 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
 #pragma unroll
         for (int i = j + 1; i < B; ++i) {
           if (i < b) {
-            const double rji = kr_lane(x[j], i);
+            const double rji = lane_value(x[j], i);
             if (l >= i && l < b) x[i] -= rji * x[j];
           }
         }
@@ -241,8 +235,8 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
       double s = 0.0;   // minus the sum
 #pragma unroll
       for (int k = i + 1; k < B; ++k)
-        if (k < b) s -= kr_lane(x[i], k) * y[k];
-      const double rii = kr_lane(x[i], i);
+        if (k < b) s -= lane_value(x[i], k) * y[k];
+      const double rii = lane_value(x[i], i);
       y[i] = i == l ? 1.0 / rii : (i < l ? s / rii : 0.0);
     }
   }
@@ -266,19 +260,6 @@ __global__ __launch_bounds__(64) void k_kr_chol(const double* __restrict__ A, in
 // product with R^-1 takes the tile through LDS into row-major operand order and
 // leaves it as it was held.  Measured at n = 1000: 83 us of kernels and nine
 // launches -> 24 us and one (12 us at n = 216, 47 us at n = 1900).
-template <int I>
-__device__ __forceinline__ double kr_bcast(double x) {
-  return __builtin_amdgcn_mov_dpp(x, 0x150 + I, 0xf, 0xf, true);
-}
-template <int... I, class F>
-__device__ __forceinline__ void kr_for_impl(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void kr_for(F&& f) {
-  kr_for_impl(std::make_integer_sequence<int, N>{}, f);
-}
-
 constexpr int KR_QR_WAVES = 8;   // waves holding rows; one more factorises
 constexpr int KR_QR_TS = 17;     // row stride of a tile in LDS
 
@@ -300,25 +281,25 @@ __global__ __launch_bounds__(64 * (KR_QR_WAVES + 1)) void k_kr_cholqr3(const dou
 #pragma unroll
       for (int i = 0; i < 16; ++i) x[i] = gm[i * 16 + j];
       double dmax = 0.0, tr = 0.0;
-      kr_for<16>([&](auto ii) __attribute__((always_inline)) {
+      static_for<16>([&](auto ii) __attribute__((always_inline)) {
         constexpr int i = decltype(ii)::value;
-        tr += kr_bcast<i>(x[i]);
+        tr += row_bcast<i>(x[i]);
       });
       const double sh = pass == 0 ? 11.0 * ((double)n * 16 + 16.0 * 17) * 0x1p-53 * tr : 0.0;
       int jj = j;
       asm volatile("" : "+v"(jj));   // compared here: the sixteen masks kept over the passes spill
-      kr_for<16>([&](auto ii) __attribute__((always_inline)) {
+      static_for<16>([&](auto ii) __attribute__((always_inline)) {
         constexpr int i = decltype(ii)::value;
         x[i] += jj == i ? sh : 0.0;
         z[i] = jj == i ? 1.0 : 0.0;
-        dmax = fmax(dmax, kr_bcast<i>(x[i]));
+        dmax = fmax(dmax, row_bcast<i>(x[i]));
       });
       // R in the upper triangle: lane k holds R[i][k] in x[i], k >= i (entries
       // below it are not read).  The same row operations on the identity leave
       // column j of R^-T in z, with the factorisation's own broadcasts.
-      kr_for<16>([&](auto cc) __attribute__((always_inline)) {
+      static_for<16>([&](auto cc) __attribute__((always_inline)) {
         constexpr int c = decltype(cc)::value;
-        const double d = kr_bcast<c>(x[c]);
+        const double d = row_bcast<c>(x[c]);
         const bool ok = d > 1e-14 * dmax;   // a dependent column is dropped
         const double dd = ok ? d : 1.0;
         double y = __builtin_amdgcn_rsq(dd);   // 1 / sqrt, refined twice
@@ -329,9 +310,9 @@ __global__ __launch_bounds__(64 * (KR_QR_WAVES + 1)) void k_kr_cholqr3(const dou
         y = ok ? y : 0.0;
         x[c] *= y;
         z[c] *= y;
-        kr_for<15 - c>([&](auto ii) __attribute__((always_inline)) {
+        static_for<15 - c>([&](auto ii) __attribute__((always_inline)) {
           constexpr int i = decltype(ii)::value + c + 1;
-          const double r = -kr_bcast<i>(x[c]);
+          const double r = -row_bcast<i>(x[c]);
           x[i] = fma(r, x[c], x[i]);
           z[i] = fma(r, z[c], z[i]);
         });

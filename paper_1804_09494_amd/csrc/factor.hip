@@ -11,6 +11,7 @@
 #include <cmath>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace tk {
 
@@ -68,105 +69,215 @@ __global__ __launch_bounds__(256) void k_uw(const float* __restrict__ Y, int64_t
 typedef float floatx4_f __attribute__((ext_vector_type(4)));
 typedef double doublex4_f __attribute__((ext_vector_type(4)));
 
-// Combine the four waves' 16x16 Gram tiles in wave order and write the K x K
-// block of this workgroup.  Register r of lane l holds G[row][l%16] with
-// row = 4*(l/16) + r for the FP32 MFMA and row = l/16 + 4*r for the FP64 one.
-template <bool F64LAYOUT, class T4>
-__device__ __forceinline__ void write_gram_part(const T4& g, int K, double* red, double* __restrict__ part) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w)
+constexpr int UW_WAVES = 16;      // waves per workgroup of the K <= 16 kernels, at most
+constexpr int UW_SH = 32;         // doubles of scratch scaled_w needs
+
+// The waves' Grams, summed in wave order: this workgroup's K x K partial.
+// Register r of lane (q, j) = (l/16, l%16) holds entry (q + 4r, j); tiles: 256
+// doubles per wave, free in every wave.
+__device__ __forceinline__ void write_gram_part(const doublex4_f& g, int K, double* tiles, double* __restrict__ part) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double* dst = red + r * 64 + lane;
-        *dst = (w == 0) ? (double)g[r] : *dst + (double)g[r];
-      }
-    __syncthreads();
-  }
+  for (int r = 0; r < 4; ++r) tiles[wave * 256 + ((lane >> 4) + 4 * r) * 16 + (lane & 15)] = g[r];
+  __syncthreads();
   if (threadIdx.x < 256) {
-    const int r = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int a = F64LAYOUT ? (l >> 4) + 4 * r : 4 * (l >> 4) + r, b = l & 15;
-    if (a < K && b < K) part[(int64_t)blockIdx.x * K * K + a * K + b] = red[threadIdx.x];
+    double s = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += tiles[w * 256 + threadIdx.x];
+    const int a = threadIdx.x >> 4, b = threadIdx.x & 15;
+    if (a < K && b < K) part[(int64_t)blockIdx.x * K * K + a * K + b] = s;
   }
 }
 
-// U = Y W on the matrix cores (K <= 16): v_mfma_f32_16x16x4_f32 over 16-row
-// tiles, one tile per wave at a time.  Lane l reads four consecutive columns
-// (s + 4*(l/16) .. +3) of row l%16 of the tile; MFMA u contracts column
-// s + 4k + u of Y (k = l/16) with row s + 4k + u of W.  The result tile gives
-// U (stored FP64) and, with the same registers as both operands, the
-// workgroup's partial U^T U.  VEC: khat % 4 == 0 (16-byte loads).
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_uw_mfma(const float* __restrict__ Y, int64_t R, int khat,
-                                                 const double* __restrict__ W, int K, double* __restrict__ U,
-                                                 double* __restrict__ part) {
-  __shared__ double red[256];
-  extern __shared__ float wl[];   // kpad x 16, FP32, zero beyond khat and K
+// W = V_K diag(lam)^(-1/2).  A column whose eigenvalue is at or below the
+// Gram's rounding floor is not a direction of Y: an exactly zero singular
+// value of Y shows up in the FP32 Gram as an eigenvalue of the size of the
+// Gram's rounding error, below u ||Y||_F^2 (u = 2^-24), so eigenvalues up to
+// RANK_FLOOR * trace(G) are taken as zero.  Such a column sets flag bit 2
+// (rank deficiency) and gets W = 0.  Above the floor a small eigenvalue is
+// kept: its vector is only as accurate as the Gram allows, but it lies in the
+// range of Y.
+constexpr double RANK_FLOOR = 4.0 / 16777216.0;   // 4 u
+
+// What the kernels below form W from: lam null: W = VK as given.  diag[i *
+// dstride], i < khat: the Gram's diagonal (dstride = khat + 1 in the Gram
+// itself, 1 for a separate vector).
+struct FactorW {
+  const double* VK;    // khat x K
+  const double* lam;
+  const double* diag;
+  int64_t dstride;
+  int* flag;           // set to the failure bits of W (0 or 2)
+  int* kvalid;         // columns above the floor
+};
+
+// W as the B operand of the FP32 MFMA in LDS: wl[16 c + j], zero beyond khat
+// and K.  Every workgroup forms its own (a launch and a trip through memory
+// less); `first` also writes the flag and the count.
+__device__ __forceinline__ void scaled_w(const FactorW& w, int khat, int K, bool first, double* sh, float* wl) {
   const int kpad = (khat + 15) & ~15;
-  for (int i = threadIdx.x; i < kpad * 16; i += blockDim.x) {
-    const int c = i >> 4, j = i & 15;
-    wl[i] = (c < khat && j < K) ? (float)W[(int64_t)c * K + j] : 0.f;
-  }
-  __syncthreads();
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int i16 = lane & 15, q = lane >> 4;
-  floatx4_f g = {0.f, 0.f, 0.f, 0.f};
-  const int64_t ntile = (R + 15) >> 4;
-  for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntile; t += (int64_t)gridDim.x * 4) {
-    const int64_t row = t * 16 + i16;
-    const bool rok = row < R;
-    const float* yr = Y + row * khat;
-    floatx4_f c = {0.f, 0.f, 0.f, 0.f};
-    // four 16-column steps per iteration, their loads issued before the first
-    // MFMA (the MFMAs keep their order: same U as one step at a time)
-    for (int s = 0; s < kpad; s += 64) {
-      float y[4][4];
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const int col = s + 16 * d + 4 * q;
-        if (VEC) {
-          const float4 v = (rok && col < khat) ? *reinterpret_cast<const float4*>(yr + col) : float4{0.f, 0.f, 0.f, 0.f};
-          y[d][0] = v.x; y[d][1] = v.y; y[d][2] = v.z; y[d][3] = v.w;
-        } else {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) y[d][u] = (rok && col + u < khat) ? yr[col + u] : 0.f;
-        }
-      }
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        if (s + 16 * d >= kpad) break;   // the same in every lane
-        const int col = s + 16 * d + 4 * q;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          c = __builtin_amdgcn_mfma_f32_16x16x4f32(y[d][u], wl[(col + u) * 16 + i16], c, 0, 0, 0);
+  const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  if (w.lam) {
+    double t = 0.0;
+    for (int i = threadIdx.x; i < khat; i += blockDim.x) t += w.diag[(int64_t)i * w.dstride];
+    for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d);
+    if ((threadIdx.x & 63) == 0) sh[wave] = t;
+    __syncthreads();
+    double tr = 0.0;
+    for (int i = 0; i < waves; ++i) tr += sh[i];
+    const double floor_ = RANK_FLOOR * tr;
+    if (threadIdx.x < 16) {
+      const int k = threadIdx.x;
+      const bool ok = k < K && k < khat && w.lam[k] > floor_ && w.lam[k] > 0.0;   // only khat eigenpairs exist
+      sh[16 + k] = ok ? 1.0 / sqrt(w.lam[k]) : 0.0;
+      const unsigned good = (unsigned)__ballot(ok) & 0xffffu;
+      if (first && k == 0) {   // eigenvalues come in descending order
+        w.kvalid[0] = __ffs(~good) - 1;
+        w.flag[0] = good == (1u << K) - 1 ? 0 : 2;
       }
     }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < kpad * 16; i += blockDim.x) {
+    const int c = i >> 4, j = i & 15;
+    const double sc = w.lam ? sh[16 + j] : 1.0;
+    wl[i] = (c < khat && j < K && sc != 0.0) ? (float)(w.VK[(int64_t)c * K + j] * sc) : 0.f;
+  }
+  __syncthreads();
+}
+
+// U's 16-row tile t = Y W by v_mfma_f32_16x16x4_f32: lane l reads four
+// consecutive columns (s + 4*(l/16) .. +3) of row l%16 of the tile; MFMA u
+// contracts column s + 4k + u of Y (k = l/16) with row s + 4k + u of W.
+// Register r of lane (q, j) is U[4q + r][j].  VEC: khat % 4 == 0 (16-byte loads).
+template <bool VEC>
+__device__ __forceinline__ floatx4_f uw_tile(const float* __restrict__ Y, int64_t R, int khat, const float* wl,
+                                             int64_t t) {
+  const int lane = threadIdx.x & 63;
+  const int i16 = lane & 15, q = lane >> 4;
+  const int kpad = (khat + 15) & ~15;
+  const int64_t row = t * 16 + i16;
+  const bool rok = row < R;
+  const float* yr = Y + row * khat;
+  floatx4_f c = {0.f, 0.f, 0.f, 0.f};
+  // four 16-column steps per iteration, their loads issued before the first
+  // MFMA (the MFMAs keep their order: same U as one step at a time)
+  for (int s = 0; s < kpad; s += 64) {
+    float y[4][4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int col = s + 16 * d + 4 * q;
+      if (VEC) {
+        const float4 v = (rok && col < khat) ? *reinterpret_cast<const float4*>(yr + col) : float4{0.f, 0.f, 0.f, 0.f};
+        y[d][0] = v.x; y[d][1] = v.y; y[d][2] = v.z; y[d][3] = v.w;
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[d][u] = (rok && col + u < khat) ? yr[col + u] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      if (s + 16 * d >= kpad) break;   // the same in every lane
+      const int col = s + 16 * d + 4 * q;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(y[d][u], wl[(col + u) * 16 + i16], c, 0, 0, 0);
+    }
+  }
+  return c;
+}
+
+// U = Y W on the matrix cores (K <= 16), one 16-row tile per wave at a time;
+// bounded by the read of Y.  At most 256 workgroups of 4 to 16 waves, so that
+// the step after sums at most 256 partials.  ROWS: U's rows go to dF at their
+// slices in FP32 and nothing else is written; else U (FP64) and the
+// workgroup's partial U^T U (FP64 MFMA of the same registers).
+template <bool VEC, bool ROWS>
+__global__ __launch_bounds__(64 * UW_WAVES) void k_uw_mfma(const float* __restrict__ Y, int64_t R, int khat,
+                                                           FactorW w, int K, double* __restrict__ U,
+                                                           double* __restrict__ part,
+                                                           const int32_t* __restrict__ row_slice,
+                                                           float* __restrict__ dF) {
+  extern __shared__ __align__(16) double shd[];   // UW_SH, then W (or the waves' Grams)
+  float* wl = reinterpret_cast<float*>(shd + UW_SH);
+  scaled_w(w, khat, K, blockIdx.x == 0, shd, wl);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int waves = blockDim.x >> 6;
+  const int i16 = lane & 15, q = lane >> 4;
+  doublex4_f g = {0.0, 0.0, 0.0, 0.0};
+  const int64_t ntile = (R + 15) >> 4;
+  for (int64_t t = (int64_t)blockIdx.x * waves + wave; t < ntile; t += (int64_t)gridDim.x * waves) {
+    const floatx4_f c = uw_tile<VEC>(Y, R, khat, wl, t);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t rr = t * 16 + 4 * q + r;
-      if (rr < R && i16 < K) U[rr * K + i16] = (double)c[r];
+      if (rr < R && i16 < K) {
+        if (ROWS)
+          dF[(int64_t)row_slice[rr] * K + i16] = c[r];
+        else
+          U[rr * K + i16] = (double)c[r];
+      }
     }
+    if (!ROWS)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) g = __builtin_amdgcn_mfma_f32_16x16x4f32(c[r], c[r], g, 0, 0, 0);
+      for (int r = 0; r < 4; ++r) g = __builtin_amdgcn_mfma_f64_16x16x4f64((double)c[r], (double)c[r], g, 0, 0, 0);
   }
-  write_gram_part<false>(g, K, red, part);
+  if (!ROWS) {
+    __syncthreads();   // every wave has read its last W
+    write_gram_part(g, K, shd + UW_SH, part);
+  }
+}
+
+// flag[0]: this mode's failure bits; flag[1]: 1 + the first failed mode of the invocation
+__device__ __forceinline__ void record_flag(int* flag, int n, int bits) {
+  flag[FLAG_BITS + n] = bits;
+  if (bits && !flag[1]) flag[1] = n + 1;
+}
+
+// Where the last product writes the factor: its FP64 master (slice order) and
+// its FP32 working copy (storage labels), unless an earlier mode of a deferred
+// invocation failed.
+struct FactorOut {
+  const int32_t* row_slice;
+  const int32_t* label;
+  double* F64;
+  float* F32;
+  int kp32;
+  int* flag;
+  int n;
+  int deferred;   // flag[1] skips the writes
+  int record;     // this mode's bits are recorded (record_flag)
+};
+
+// flag[1] may already be this mode's own (recorded by a faster workgroup)
+__device__ __forceinline__ bool skip_writes(const FactorOut& o) {
+  if (!o.deferred) return false;
+  const int a = o.flag[1];
+  return a != 0 && a != o.n + 1;
+}
+
+__device__ __forceinline__ void write_factor(const FactorOut& o, int64_t rr, int K, int k, double v) {
+  const int64_t l = o.row_slice[rr];
+  o.F64[l * K + k] = v;
+  o.F32[(int64_t)o.label[l] * o.kp32 + k] = (float)v;
 }
 
 // U <- U Rinv on the FP64 matrix cores (K <= 16), 16-row tiles: lane l supplies
 // A[i = l%16][k = l/16] = U[row i][4s + k] and B[k][j = l%16] = Rinv[4s + k][j]
-// for s = 0..3; v_mfma_f64_16x16x4_f64 returns D[l/16 + 4r][l%16] in register r.  Not FINAL: write U back and the partial U^T U of the result.
-// FINAL: write the rows straight into the factor's FP64 master (slice order)
-// and its FP32 working copy (storage labels).
+// for s = 0..3; v_mfma_f64_16x16x4_f64 returns D[l/16 + 4r][l%16] in register r.
+// Not FINAL: write U back and the partial U^T U of the result.  FINAL: write
+// the rows straight into the factor.
 template <bool FINAL>
-__global__ __launch_bounds__(256) void k_rinv_mfma(double* __restrict__ U, int64_t R, int K,
-                                                   const double* __restrict__ Rinv, double* __restrict__ part,
-                                                   const int32_t* __restrict__ row_slice,
-                                                   const int32_t* __restrict__ label, double* __restrict__ F64,
-                                                   float* __restrict__ F32, int kp32, const int* __restrict__ abort) {
-  // FINAL: an earlier mode of this invocation failed; keep this factor as it was
-  if (FINAL && abort && *abort) return;
-  __shared__ double red[256];
+__global__ __launch_bounds__(64 * UW_WAVES) void k_rinv_mfma(double* __restrict__ U, int64_t R, int K,
+                                                             const double* __restrict__ Rinv,
+                                                             double* __restrict__ part, FactorOut o) {
+  extern __shared__ __align__(16) double shd[];   // not FINAL: 256 per wave
+  if (FINAL) {
+    const bool skip = skip_writes(o);
+    if (o.record && blockIdx.x == 0 && threadIdx.x == 0) record_flag(o.flag, o.n, o.flag[0]);
+    if (skip) return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int waves = blockDim.x >> 6;
   const int i16 = lane & 15, q = lane >> 4;
   double rb[4];
 #pragma unroll
@@ -176,28 +287,23 @@ __global__ __launch_bounds__(256) void k_rinv_mfma(double* __restrict__ U, int64
   }
   doublex4_f g = {0.0, 0.0, 0.0, 0.0};
   const int64_t ntile = (R + 15) >> 4;
-  for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntile; t += (int64_t)gridDim.x * 4) {
-    const int64_t row = t * 16 + i16;
-    const bool rok = row < R;
+  for (int64_t t = (int64_t)blockIdx.x * waves + wave; t < ntile; t += (int64_t)gridDim.x * waves) {
+    const double* ur = U + min(t * 16 + i16, R - 1) * K;
     doublex4_f c = {0.0, 0.0, 0.0, 0.0};
+    double a[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int k = 4 * s + q;
-      const double a = (rok && k < K) ? U[row * K + k] : 0.0;
-      c = __builtin_amdgcn_mfma_f64_16x16x4f64(a, rb[s], c, 0, 0, 0);
-    }
+    for (int s = 0; s < 4; ++s) a[s] = ur[min(4 * s + q, K - 1)];   // all loads at once
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(t * 16 + i16 < R && 4 * s + q < K ? a[s] : 0.0, rb[s], c, 0, 0, 0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t rr = t * 16 + q + 4 * r;
       if (rr < R && i16 < K) {
-        if (FINAL) {
-          const int64_t l = row_slice[rr];
-          const int64_t sl = label[l];
-          F64[l * K + i16] = c[r];
-          F32[sl * kp32 + i16] = (float)c[r];
-        } else {
+        if (FINAL)
+          write_factor(o, rr, K, i16, c[r]);
+        else
           U[rr * K + i16] = c[r];
-        }
       }
     }
     if (!FINAL) {
@@ -207,7 +313,7 @@ __global__ __launch_bounds__(256) void k_rinv_mfma(double* __restrict__ U, int64
       for (int r = 0; r < 4; ++r) g = __builtin_amdgcn_mfma_f64_16x16x4f64(c[r], c[r], g, 0, 0, 0);
     }
   }
-  if (!FINAL) write_gram_part<true>(g, K, red, part);
+  if (!FINAL) write_gram_part(g, K, shd, part);
 }
 
 // U <- U Rinv (upper triangular, K x K) and partial U^T U of the result, over
@@ -270,143 +376,199 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ pa
   }
 }
 
-// Row j of A beyond the diagonal is exactly zero.  A column of U zeroed below
-// the rank floor (W = 0, so U's column is exactly 0.0) has an exactly zero row
-// and column in A = U^T U, and every earlier step leaves them so: the Cholesky
-// steps below take R[j][j] = 1 for it, so that U R^-1 keeps it zero and the
-// other columns come out orthonormal; it is not a failure (the completion adds
-// that direction).
-__device__ __forceinline__ bool zero_row(const double* A, int K, int j) {
-  for (int i = j + 1; i < K; ++i)
-    if (A[j * K + i] != 0.0) return false;
-  return true;
-}
-
-// Cholesky A = R^T R of the summed K x K matrix, Rinv = R^-1.
-// flag bit 0 set when a pivot is not positive relative to the largest diagonal.
-__global__ void k_chol_inv(const double* __restrict__ Asum, int K, double* __restrict__ Rinv, int* __restrict__ flag) {
-  extern __shared__ double shd[];
-  double* A = shd;          // K * K
-  double* Rm = A + K * K;   // K * K
-  for (int i = threadIdx.x; i < K * K; i += blockDim.x) A[i] = Asum[i];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double dmax = 0.0;
-    for (int i = 0; i < K; ++i) dmax = fmax(dmax, A[i * K + i]);
-    bool ok = dmax > 0.0;
-    for (int i = 0; i < K * K; ++i) Rm[i] = 0.0;
-    for (int j = 0; j < K && ok; ++j) {
-      double d = A[j * K + j];
-      for (int k = 0; k < j; ++k) d -= Rm[k * K + j] * Rm[k * K + j];
-      if (A[j * K + j] == 0.0 && d == 0.0 && zero_row(A, K, j)) {   // a zeroed column stays zero (R[j][j] = 1)
-        Rm[j * K + j] = 1.0;
-        continue;
-      }
-      if (!(d > 1e-16 * dmax)) { ok = false; break; }
-      const double rjj = sqrt(d);
-      Rm[j * K + j] = rjj;
-      for (int i = j + 1; i < K; ++i) {
-        double s = A[j * K + i];
-        for (int k = 0; k < j; ++k) s -= Rm[k * K + j] * Rm[k * K + i];
-        Rm[j * K + i] = s / rjj;
-      }
-    }
-    if (!ok) {
-      flag[0] |= 1;
-      for (int i = 0; i < K * K; ++i) Rinv[i] = (i / K == i % K) ? 1.0 : 0.0;
-    } else {
-      // inverse of upper triangular R, column by column
-      for (int i = 0; i < K * K; ++i) Rinv[i] = 0.0;
-      for (int j = 0; j < K; ++j) {
-        Rinv[j * K + j] = 1.0 / Rm[j * K + j];
-        for (int i = j - 1; i >= 0; --i) {
-          double s = 0.0;
-          for (int k = i + 1; k <= j; ++k) s += Rm[i * K + k] * Rinv[k * K + j];
-          Rinv[i * K + j] = -s / Rm[i * K + i];
-        }
-      }
-    }
-  }
-}
-
-// The same for K <= 16 with one wavefront: right-looking Cholesky (lanes over
-// the trailing block), then column c of R^-1 by back substitution in lane c.
-__global__ __launch_bounds__(64) void k_chol_inv_wave(const double* __restrict__ Asum, int K,
-                                                      double* __restrict__ Rinv, int* __restrict__ flag) {
-  __shared__ double A[16 * 16];
-  __shared__ double rdiag[16];
-  __shared__ int okf;
-  const int l = threadIdx.x;
-  for (int i = l; i < K * K; i += 64) A[i] = Asum[i];
-  if (l == 0) okf = 1;
-  __syncthreads();
+// One wavefront: column j = lane of R^-T (z[i] = R^-1[j][i]) for A = R^T R, A
+// symmetric K x K in LDS (row stride NP, at least 16), K <= NP.  Lane j keeps
+// column j of A and of the identity, both under the factorisation's row
+// operations; the other columns' entries come across lanes (rows of 16 lanes
+// alike for NP <= 16), so nothing waits on LDS: 5.9 us of kernel at K = 5 and
+// 11.8 us at K = 10 with the matrix in LDS, 5.7 us at K = 10 with the partials'
+// sum (2.8 to 4.6 us before) in the same launch.
+// False when a pivot is not positive relative to the largest diagonal.  A
+// column of U zeroed below the rank floor (W = 0, so U's column is exactly 0.0)
+// has an exactly zero row and column in A = U^T U, and every earlier step
+// leaves them so: R[j][j] = 1 is taken for it, so that U R^-1 keeps it zero and
+// the other columns come out orthonormal; it is not a failure (the completion
+// adds that direction).
+template <int NP>
+__device__ __forceinline__ bool chol_rinv(const double* A, int K, double (&z)[NP]) {
+  constexpr int LS = NP <= 16 ? 16 : NP;
+  int j = threadIdx.x & (LS - 1);
+  asm volatile("" : "+v"(j));   // compared here: masks kept over a caller's loop spill
+  double x[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) x[i] = (i < K && j < K) ? A[i * LS + j] : 0.0;
+  auto entry = [&](auto row, auto col) __attribute__((always_inline)) {
+    constexpr int r = decltype(row)::value, c = decltype(col)::value;
+    if constexpr (NP <= 16)
+      return row_bcast<c>(x[r]);
+    else
+      return lane_value(x[r], c);
+  };
   double dmax = 0.0;
-  for (int i = 0; i < K; ++i) dmax = fmax(dmax, A[i * K + i]);
-  if (!(dmax > 0.0) && l == 0) okf = 0;
+  uint32_t zero = 0;
+  static_for<NP>([&](auto ii) __attribute__((always_inline)) {
+    constexpr int i = decltype(ii)::value;
+    const double d = entry(ii, ii);
+    dmax = fmax(dmax, d);   // the padding's zeros change nothing
+    zero |= d == 0.0 ? 1u << i : 0u;
+    z[i] = j == i ? 1.0 : 0.0;
+  });
+  bool ok = dmax > 0.0;
+  static_for<NP>([&](auto cc) __attribute__((always_inline)) {
+    constexpr int c = decltype(cc)::value;
+    if (c >= K) return;   // the same in every lane
+    const double d = entry(cc, cc);
+    const bool none = __ballot(j > c && x[c] != 0.0) == 0;   // row c beyond the diagonal is exactly zero
+    const bool zr = ((zero >> c) & 1) && d == 0.0 && none;
+    const bool pos = d > 1e-16 * dmax;
+    ok = ok && (pos || zr);
+    const double dd = pos ? d : 1.0;
+    double y = __builtin_amdgcn_rsq(dd);   // 1 / sqrt, refined twice
+    double e = fma(-dd * y, y, 1.0);
+    y = fma(0.5 * y, e, y);
+    e = fma(-dd * y, y, 1.0);
+    y = fma(0.5 * y, e, y);
+    x[c] *= y;
+    z[c] *= y;
+    static_for<NP - 1 - c>([&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value + c + 1;
+      const double r = -entry(cc, std::integral_constant<int, i>{});
+      x[i] = fma(r, x[c], x[i]);
+      z[i] = fma(r, z[c], z[i]);
+    });
+  });
+  return ok;
+}
+
+// Rinv = R^-1 of the Cholesky factor of the sum of nparts K x K blocks (in
+// fixed order), in one workgroup; the identity and flag bit 1 when it fails.
+// NP = 32: one block only.
+template <int NP>
+__global__ __launch_bounds__(NP <= 16 ? 1024 : 256) void k_sum_chol(const double* __restrict__ part, int nparts, int K,
+                                                                    double* __restrict__ Rinv,
+                                                                    int* __restrict__ flag) {
+  constexpr int LS = NP <= 16 ? 16 : NP;
+  __shared__ double A[LS * LS];
+  __shared__ double acc[1024];
+  const int E = K * K;
+  if (NP <= 16) {
+    // a group of threads per share of the blocks, a thread per entry
+    const int gs = E <= 64 ? 64 : E <= 128 ? 128 : 256, G = 1024 / gs;
+    const int e = threadIdx.x & (gs - 1), g = threadIdx.x / gs;
+    double s = 0.0;
+    if (e < E)
+      for (int p = g; p < nparts; p += 8 * G) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)min(p + u * G, nparts - 1) * E + e];   // loads together
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += p + u * G < nparts ? v[u] : 0.0;
+      }
+    acc[threadIdx.x] = s;
+    __syncthreads();
+    if ((int)threadIdx.x < E) {
+      double t = 0.0;
+      for (int h = 0; h < G; ++h) t += acc[h * gs + threadIdx.x];
+      A[(threadIdx.x / K) * LS + threadIdx.x % K] = t;
+    }
+  } else {
+    for (int i = threadIdx.x; i < E; i += blockDim.x) A[(i / K) * LS + i % K] = part[i];
+  }
   __syncthreads();
-  // A = R^T R, R stored in the upper triangle of A (row j: R[j][j..K-1])
-  for (int j = 0; j < K && okf; ++j) {
-    const double d = A[j * K + j];
-    const bool zr = Asum[j * K + j] == 0.0 && d == 0.0 && zero_row(A, K, j);   // the same in every lane
-    __syncthreads();
-    if (zr) {   // a zeroed column stays zero (R[j][j] = 1); its row of R is zero
-      if (l == 0) { A[j * K + j] = 1.0; rdiag[j] = 1.0; }
-      __syncthreads();
-      continue;
-    }
-    if (!(d > 1e-16 * dmax)) {
-      if (l == 0) okf = 0;
-      __syncthreads();
-      break;
-    }
-    const double r = sqrt(d);
-    const double ri = 1.0 / r;
-    // row j of R: R[j][i] = A[j][i] / r for i > j
-    if (l > j && l < K) A[j * K + l] *= ri;
-    if (l == 0) { A[j * K + j] = r; rdiag[j] = ri; }
-    __syncthreads();
-    // trailing update A[i][k] -= R[j][i] R[j][k], i, k > j (upper triangle)
-    for (int q = l; q < K * K; q += 64) {
-      const int i = q / K, k = q - i * K;
-      if (i > j && k >= i) A[i * K + k] -= A[j * K + i] * A[j * K + k];
-    }
-    __syncthreads();
+  if (threadIdx.x >= 64) return;
+  double z[NP];
+  const bool ok = chol_rinv<NP>(A, K, z);
+  const int j = threadIdx.x;
+  if (!ok && j == 0) flag[0] |= 1;
+  if (j < K)
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      if (i < K) Rinv[j * K + i] = ok ? z[i] : (i == j ? 1.0 : 0.0);
+}
+
+// The whole factor step of a mode with few rows (R <= 16 UW_WAVES, K <= 16) in
+// one workgroup: U = Y W, both CholeskyQR passes and the factor's rows, with U
+// in registers (a 16-row tile per wave) throughout.  Such a step is all
+// latency: with ten launches it took 39 us at R = 200, Khat = 25, as one 11 us.
+// A tile's product with R^-1 goes through LDS into
+// row-major operand order; the row order inside a tile stays that of uw_tile.
+template <bool VEC, int NP>
+__global__ __launch_bounds__(64 * UW_WAVES) void k_factor_wg(const float* __restrict__ Y, int R, int khat, FactorW w,
+                                                             int K, FactorOut o) {
+  constexpr int TS = 17;   // row stride of a tile in LDS
+  extern __shared__ __align__(16) double shd[];
+  double* tiles = shd;                             // a tile per wave; the waves' Grams
+  double* gm = tiles + UW_WAVES * 16 * TS;         // 16 x 16
+  double* ri = gm + 256;                           // 16 x 16
+  double* sh = ri + 256;                           // UW_SH
+  float* wl = reinterpret_cast<float*>(sh + UW_SH);
+  __shared__ int bad;
+  const int lane = threadIdx.x & 63, j = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool skip = skip_writes(o);
+  if (threadIdx.x == 0) bad = 0;
+  scaled_w(w, khat, K, true, sh, wl);
+  const int ntile = (R + 15) >> 4;
+  doublex4_f u = {0.0, 0.0, 0.0, 0.0};
+  if (wave < ntile) {
+    const floatx4_f c = uw_tile<VEC>(Y, R, khat, wl, wave);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) u[r] = (double)c[r];
   }
-  if (!okf) {
-    if (l == 0) flag[0] |= 1;
-    for (int i = l; i < K * K; i += 64) Rinv[i] = (i / K == i % K) ? 1.0 : 0.0;
-    return;
-  }
-  // column c of R^-1 (upper triangular): X[c][c] = 1/R[c][c], X[i][c] = -(sum_{k=i+1..c} R[i][k] X[k][c]) / R[i][i]
-  __shared__ double X[16 * 16];   // X[c][i] = R^-1[i][c] (LDS: a runtime-indexed register array would spill)
-  if (l < K) {
-    const int c = l;
-    double* x = X + c * 16;
-    for (int i = 0; i < K; ++i) x[i] = 0.0;
-    x[c] = rdiag[c];
-    for (int i = c - 1; i >= 0; --i) {
-      double s = 0.0;
-      for (int k = i + 1; k <= c; ++k) s += A[i * K + k] * x[k];
-      x[i] = -s * rdiag[i];
+  double* mine = tiles + wave * 16 * TS;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    doublex4_f g = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) g = __builtin_amdgcn_mfma_f64_16x16x4f64(u[r], u[r], g, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mine[(q + 4 * r) * 16 + j] = g[r];
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      double t = 0.0;
+#pragma unroll
+      for (int v = 0; v < UW_WAVES; ++v) t += tiles[v * 16 * TS + threadIdx.x];
+      gm[threadIdx.x] = t;
     }
-    for (int i = 0; i < K; ++i) Rinv[i * K + c] = x[i];
+    __syncthreads();
+    if (wave == 0) {
+      double z[NP];
+      const bool ok = chol_rinv<NP>(gm, K, z);
+      if (!ok && lane == 0) bad = 1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const double v = i < NP ? z[i < NP ? i : 0] : 0.0;
+        ri[j * 16 + i] = j < K && i < K ? (ok ? v : (i == j ? 1.0 : 0.0)) : 0.0;   // the rows of 16 lanes alike
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mine[(q + 4 * r) * TS + j] = u[r];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    doublex4_f d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      d = __builtin_amdgcn_mfma_f64_16x16x4f64(mine[j * TS + 4 * s + q], ri[(4 * s + q) * 16 + j], d, 0, 0, 0);
+    u = d;
+    __syncthreads();   // the tiles' places become the Grams' again
+  }
+  if (threadIdx.x == 0) {
+    const int bits = o.flag[0] | bad;   // written by this thread in scaled_w
+    o.flag[0] = bits;
+    if (o.record) record_flag(o.flag, o.n, bits);
+  }
+  if (skip) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int rr = 16 * wave + 4 * q + r;
+    if (rr < R && j < K) write_factor(o, rr, K, j, u[r]);
   }
 }
 
-// W = V_K diag(lam)^(-1/2); a column with a non-positive or negligible
-// eigenvalue (relative to the largest) is zeroed and flagged (bit 1).
-// W = V_K diag(lam)^(-1/2).  A column whose eigenvalue is at or below the
-// Gram's rounding floor is not a direction of Y: an exactly zero singular
-// value of Y shows up in the FP32 Gram as an eigenvalue of the size of the
-// Gram's rounding error, below u ||Y||_F^2 (u = 2^-24), so eigenvalues up to
-// RANK_FLOOR * trace(G) are taken as zero.  Such a column sets flag bit 2
-// (rank deficiency) and gets W = 0.  Above the floor a small eigenvalue is
-// kept: its vector is only as accurate as the Gram allows, but it lies in the
-// range of Y.
-constexpr double RANK_FLOOR = 4.0 / 16777216.0;   // 4 u
-
-// diag[i * dstride], i < khat: the Gram's diagonal (dstride = khat + 1 in the
-// Gram itself, 1 for a separate vector).
+// W of scaled_w in memory (khat x K), for ranks above 16 and for W too large
+// for LDS; the flag's bit is set, not cleared.
 __global__ __launch_bounds__(256) void k_make_w(const double* __restrict__ VK, const double* __restrict__ lam,
                                                 const double* __restrict__ diag, int64_t dstride, int khat, int K,
                                                 double* __restrict__ W, int* __restrict__ flag,
@@ -779,25 +941,37 @@ static bool complete_on_device(Ctx* c, int n, int g_known) {
 void complete_factor(Ctx* c, int n, int g);
 int computed_columns(Ctx* c, const int* flag_dev, int n);
 
-// U = Y W (R x K, FP64 out) on the matrix cores for K <= 16, W khat x K in
-// FP64 (rounded to FP32 for the MFMA operands); `part` receives nwg x K x K
-// partial U^T U blocks (unused by callers that only want U).  Returns nwg.
-int uw_product(Ctx* c, const float* Y, int64_t R, int khat, const double* W, int K, double* U, double* part) {
-  TK_REQUIRE(K <= 16, TK_ERR_UNSUPPORTED, "Y W on the matrix cores: K above 16");
-  const int64_t ntile = std::max<int64_t>(1, ceil_div(R, 16));
-  const int nwg = (int)std::min<int64_t>(2048, ceil_div(ntile, 4));
-  const int kpad = (khat + 15) & ~15;
-  const size_t lds = sizeof(float) * (size_t)kpad * 16;
-  TK_REQUIRE(lds + 2048 <= c->lds_per_block, TK_ERR_UNSUPPORTED, "Y W: Khat too large for LDS");
-  if (khat % 4 == 0)
-    hipLaunchKernelGGL(k_uw_mfma<true>, dim3(nwg), dim3(256), lds, c->stream, Y, R, khat, W, K, U, part);
-  else
-    hipLaunchKernelGGL(k_uw_mfma<false>, dim3(nwg), dim3(256), lds, c->stream, Y, R, khat, W, K, U, part);
-  TK_CHECK_LAUNCH();
-  return nwg;
+namespace {
+
+// Waves per workgroup for ntile 16-row tiles: at most 256 workgroups (one per
+// CU), their waves as even as can be.
+int uw_waves(int64_t ntile) { return (int)std::min<int64_t>(UW_WAVES, std::max<int64_t>(4, ceil_div(ntile, 256))); }
+int uw_groups(int64_t ntile) { return (int)std::min<int64_t>(256, ceil_div(ntile, uw_waves(ntile))); }
+size_t uw_lds(int khat, int waves) {
+  return sizeof(double) * UW_SH + std::max(sizeof(float) * 16 * (size_t)((khat + 15) & ~15),
+                                           sizeof(double) * 256 * (size_t)waves);
 }
 
-int uw_product_parts(int64_t R) { return (int)std::min<int64_t>(2048, ceil_div(std::max<int64_t>(1, ceil_div(R, 16)), 4)); }
+}  // namespace
+
+// dF[row_slice[r]] = Y[r] W (FP32) for K <= 16 on the matrix cores, W khat x K
+// in FP64 (rounded to FP32 for the MFMA operands).
+void uw_rows(Ctx* c, const float* Y, int64_t R, int khat, const double* W, int K, const int32_t* row_slice, float* dF) {
+  TK_REQUIRE(K <= 16, TK_ERR_UNSUPPORTED, "Y W on the matrix cores: K above 16");
+  const int64_t ntile = std::max<int64_t>(1, ceil_div(R, 16));
+  const int waves = uw_waves(ntile);
+  const size_t lds = uw_lds(khat, waves);
+  TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "Y W: Khat too large for LDS");
+  const FactorW w{W, nullptr, nullptr, 0, nullptr, nullptr};
+  const dim3 g(uw_groups(ntile)), t(64 * waves);
+  if (khat % 4 == 0)
+    hipLaunchKernelGGL((k_uw_mfma<true, true>), g, t, lds, c->stream, Y, R, khat, w, K, nullptr, nullptr, row_slice,
+                       dF);
+  else
+    hipLaunchKernelGGL((k_uw_mfma<false, true>), g, t, lds, c->stream, Y, R, khat, w, K, nullptr, nullptr, row_slice,
+                       dF);
+  TK_CHECK_LAUNCH();
+}
 
 // zero a buffer (2-byte units) unless an earlier mode of this invocation failed
 __global__ void k_clear_unless(uint16_t* __restrict__ p, int64_t n16, const int* __restrict__ abort) {
@@ -806,11 +980,7 @@ __global__ void k_clear_unless(uint16_t* __restrict__ p, int64_t n16, const int*
     p[i] = 0;
 }
 
-// flag[0]: this mode's failure flag; flag[1]: 1 + the first failed mode of the invocation
-__global__ void k_flag_record(int* flag, int n) {
-  flag[FLAG_BITS + n] = flag[0];
-  if (flag[0] && !flag[1]) flag[1] = n + 1;
-}
+__global__ void k_flag_record(int* flag, int n) { record_flag(flag, n, flag[0]); }
 
 // New factor n from Y (R x khat) and the leading eigenpairs (lam_k, VK).
 // Returns true when the completion path ran.
@@ -830,7 +1000,8 @@ bool form_factor(Ctx* c, int n, const float* Y, int64_t R, int khat, const doubl
   const bool mfma = K <= 16;
   const int64_t ntile = std::max<int64_t>(1, ceil_div(R, mfma ? 16 : FT_ROWS));
   const int tiles = (int)std::max<int64_t>(1, ceil_div(ntile, 1024));
-  const int nwg = mfma ? (int)std::min<int64_t>(2048, ceil_div(ntile, 4)) : (int)ceil_div(ntile, tiles);
+  const int waves = uw_waves(ntile);
+  const int nwg = mfma ? uw_groups(ntile) : (int)ceil_div(ntile, tiles);
   ensure(c, c->U64, sizeof(double) * (size_t)std::max<int64_t>(R, 1) * K);
   ensure(c, c->small64, sizeof(double) * ((size_t)khat * K + 3 * (size_t)K * K + (size_t)nwg * K * K));
   double* W = c->small64.as<double>();
@@ -839,10 +1010,17 @@ bool form_factor(Ctx* c, int n, const float* Y, int64_t R, int khat, const doubl
   double* part = Asum + (size_t)K * K;
   double* U = c->U64.as<double>();
   const ModePlan& pl = c->plan[n];
-  TK_HIP(hipMemsetAsync(flag_dev, 0, sizeof(int), c->stream));
-  hipLaunchKernelGGL(k_make_w, dim3(grid_for((int64_t)khat * K, 256, 64)), dim3(256), 0, c->stream, VK, lam_k, gdiag,
-                     dstride, khat, K, W, flag_dev, flag_dev + FLAG_KVALID + n);
-  TK_CHECK_LAUNCH();
+  const FactorW fw{VK, lam_k, gdiag, dstride, flag_dev, flag_dev + FLAG_KVALID + n};
+  const FactorOut fo{pl.row_slice.as<int32_t>(), pl.label.as<int32_t>(), c->F64[n].as<double>(),
+                     c->F32[n].as<float>(), c->kp32[n], flag_dev, n, deferred, !check_flag};
+  // W in LDS: its kernels form it and set the flag themselves
+  const bool w_lds = mfma && R > 0 && uw_lds(khat, waves) <= c->lds_per_block;
+  if (!w_lds) {
+    TK_HIP(hipMemsetAsync(flag_dev, 0, sizeof(int), c->stream));
+    hipLaunchKernelGGL(k_make_w, dim3(grid_for((int64_t)khat * K, 256, 64)), dim3(256), 0, c->stream, VK, lam_k,
+                       gdiag, dstride, khat, K, W, flag_dev, flag_dev + FLAG_KVALID + n);
+    TK_CHECK_LAUNCH();
+  }
   // rows of empty slices (never written below) must be zero: clear the copies
   // only when something else may have written them (tk_set_factor, completion)
   auto clear_factor = [&]() {
@@ -873,23 +1051,45 @@ bool form_factor(Ctx* c, int n, const float* Y, int64_t R, int khat, const doubl
     c->fac_dirty[n] = false;
   };
   auto reduce_chol = [&]() {
-    hipLaunchKernelGGL(k_sum_parts, dim3(std::min(K * K, 1024)), dim3(256), 0, c->stream, part, nwg, K * K, Asum);
-    TK_CHECK_LAUNCH();
-    if (K <= 16)
-      hipLaunchKernelGGL(k_chol_inv_wave, dim3(1), dim3(64), 0, c->stream, Asum, K, Rinv, flag_dev);
-    else
-      hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(64), sizeof(double) * 2 * K * K, c->stream, Asum, K, Rinv,
-                         flag_dev);
+    if (K <= 8) {
+      hipLaunchKernelGGL(k_sum_chol<8>, dim3(1), dim3(1024), 0, c->stream, part, nwg, K, Rinv, flag_dev);
+    } else if (K <= 16) {
+      hipLaunchKernelGGL(k_sum_chol<16>, dim3(1), dim3(1024), 0, c->stream, part, nwg, K, Rinv, flag_dev);
+    } else {
+      hipLaunchKernelGGL(k_sum_parts, dim3(std::min(K * K, 1024)), dim3(256), 0, c->stream, part, nwg, K * K, Asum);
+      TK_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_sum_chol<32>, dim3(1), dim3(256), 0, c->stream, Asum, 1, K, Rinv, flag_dev);
+    }
     TK_CHECK_LAUNCH();
   };
-  if (R > 0 && mfma) {
-    const int kpad = (khat + 15) & ~15;
-    const size_t lds = sizeof(float) * (size_t)kpad * 16;
-    if (lds + 2048 <= c->lds_per_block) {
-      if (khat % 4 == 0)
-        hipLaunchKernelGGL(k_uw_mfma<true>, dim3(nwg), dim3(256), lds, c->stream, Y, R, khat, W, K, U, part);
+  const bool vec = khat % 4 == 0;
+  const size_t wg_lds = sizeof(double) * (UW_WAVES * 16 * 17 + 512 + UW_SH) +
+                        sizeof(float) * 16 * (size_t)((khat + 15) & ~15);
+  // One workgroup for the whole step up to a tile per wave and 2^15 entries of
+  // Y: 20 us at R = 256, Khat = 128, the five launches 28.  At R = 997,
+  // Khat = 100 (four tiles per wave) one workgroup took 43 us, they 28.
+  bool recorded = false;
+  if (w_lds && R <= 16 * UW_WAVES && R * khat <= (1 << 15) && wg_lds <= c->lds_per_block) {
+    clear_factor();
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(64 * UW_WAVES), wg_lds, c->stream, Y, (int)R, khat, fw, K, fo);
+    };
+    if (K <= 8)
+      vec ? go(k_factor_wg<true, 8>) : go(k_factor_wg<false, 8>);
+    else
+      vec ? go(k_factor_wg<true, 16>) : go(k_factor_wg<false, 16>);
+    TK_CHECK_LAUNCH();
+    recorded = true;
+  } else if (R > 0 && mfma) {
+    const dim3 g(nwg), t(64 * waves);
+    if (w_lds) {
+      const size_t lds = uw_lds(khat, waves);
+      if (vec)
+        hipLaunchKernelGGL((k_uw_mfma<true, false>), g, t, lds, c->stream, Y, R, khat, fw, K, U, part, nullptr,
+                           nullptr);
       else
-        hipLaunchKernelGGL(k_uw_mfma<false>, dim3(nwg), dim3(256), lds, c->stream, Y, R, khat, W, K, U, part);
+        hipLaunchKernelGGL((k_uw_mfma<false, false>), g, t, lds, c->stream, Y, R, khat, fw, K, U, part, nullptr,
+                           nullptr);
       TK_CHECK_LAUNCH();
     } else {
       // W too large for LDS: U = Y W as a tall-skinny FP64 product, then the
@@ -899,15 +1099,14 @@ bool form_factor(Ctx* c, int n, const float* Y, int64_t R, int khat, const doubl
       TK_CHECK_LAUNCH();
     }
     reduce_chol();
-    hipLaunchKernelGGL(k_rinv_mfma<false>, dim3(nwg), dim3(256), 0, c->stream, U, R, K, Rinv, part, nullptr, nullptr,
-                       nullptr, nullptr, 0, nullptr);
+    const size_t lds = sizeof(double) * 256 * (size_t)waves;
+    hipLaunchKernelGGL(k_rinv_mfma<false>, g, t, lds, c->stream, U, R, K, Rinv, part, fo);
     TK_CHECK_LAUNCH();
     reduce_chol();
     clear_factor();
-    hipLaunchKernelGGL(k_rinv_mfma<true>, dim3(nwg), dim3(256), 0, c->stream, U, R, K, Rinv, part,
-                       pl.row_slice.as<int32_t>(), pl.label.as<int32_t>(), c->F64[n].as<double>(),
-                       c->F32[n].as<float>(), c->kp32[n], abort);
+    hipLaunchKernelGGL(k_rinv_mfma<true>, g, t, 0, c->stream, U, R, K, Rinv, part, fo);
     TK_CHECK_LAUNCH();
+    recorded = true;
   } else if (R > 0) {
     size_t lds = sizeof(double) * ((size_t)khat * K + FT_ROWS * K) + sizeof(float) * FT_ROWS * (size_t)(khat + 1);
     if (lds <= c->lds_per_block) {
@@ -935,8 +1134,10 @@ bool form_factor(Ctx* c, int n, const float* Y, int64_t R, int khat, const doubl
     clear_factor();
   }
   if (!check_flag) {
-    hipLaunchKernelGGL(k_flag_record, dim3(1), dim3(1), 0, c->stream, flag_dev, n);
-    TK_CHECK_LAUNCH();
+    if (!recorded) {
+      hipLaunchKernelGGL(k_flag_record, dim3(1), dim3(1), 0, c->stream, flag_dev, n);
+      TK_CHECK_LAUNCH();
+    }
     return false;
   }
   int hflag[2] = {0, 0};
