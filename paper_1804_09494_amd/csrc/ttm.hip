@@ -16,6 +16,7 @@
 // None of them uses atomics: every sum runs in a fixed order.
 #include <mutex>
 
+#include "lanes.hpp"
 #include "ttm_common.hpp"
 
 namespace tk {
@@ -452,8 +453,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
 // SIMD are enough and the bins may stay those of the vector-ALU kernel: a
 // workgroup of up to eight waves per bin, each wave taking a contiguous part.
 // Nothing of the bin is staged: a lane reads its element's coordinates and value
-// straight from the layout TTM3W_IDX blocks before their use, and its factor
-// rows TTM3_RING blocks before (16 bytes per lane and 16-column plane, four lanes
+// straight from the layout two rings (of TTM3_RING blocks) before their use, and its
+// factor rows one ring before (16 bytes per lane and 16-column plane, four lanes
 // per row piece; a plane's columns past the row length re-read its last quad,
 // and only entries of Y beyond K_a or K_b come of them).  The planes go through
 // LDS (1 KB each) into operand layout.  A slice inside one wave's part goes
@@ -591,6 +592,7 @@ __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int 
       } else {
         r.v = __uint_as_float(i.v);
       }
+      asm volatile("" : "+v"(r.v));   // copied now: a copy at the loop's head would wait for the newest loads
 #pragma unroll
       for (int t = 0; t < TA; ++t) r.x[t] = *reinterpret_cast<const u32x4*>(pa + oa[t]);
 #pragma unroll
@@ -684,29 +686,360 @@ __global__ __launch_bounds__(64 * TTM3W_WAVES) void k_ttm3w_mfma(TtmArgs A, int 
 //
 // With remaining modes a, b, c (ascending), Y[row] viewed as K_a x (K_b K_c) is
 //   sum_e (val_e F_a[l_a(e)])^T (F_b[l_b(e)] (x) F_c[l_c(e)]),
-// the three-mode MFMA step with B the Kronecker row of F_b and F_c: column
-// j + K_b q of B is F_b[l_b(e)][j] F_c[l_c(e)][q], formed per lane from the LDS
-// tile (two reads and a product), and the K_b K_c columns are covered by
-// NT = ceil(K_b K_c / 16) output tiles, NT MFMAs per 4-element step (7 for
-// ranks 10, against 10 with one tile per c-index).  Column of Y:
-// i + K_a (j + K_b q).  The three rows of each element are gathered with
-// 16-byte loads into a 3 KB LDS tile per wave, as in the three-mode kernel.
-// A wave's slices that continue into a neighbouring wave keep their partial
-// rows in registers and are added to the bin's LDS rows in wave order after
-// the main loop (no atomics, deterministic).
+// the three-mode MFMA step with B the Kronecker row of F_b and F_c, its K_b K_c
+// columns spread over NT output tiles of 16.  Column of Y: i + K_a (j + K_b q).
+//
+// Lane cix of a tile's sixteen holds one of the two factors for all its tiles:
+// lanes below K_b hold F_b[cix] and take F_c[t] in tile t (q = t); the rest take
+// the remaining q >= NT, L lanes for each: F_c[q] held and F_b[t + S s] in tile t
+// (s the lane's place among the L, S = NT rounded down to a multiple of 4, or NT
+// below 4).  So a lane's changing factors are consecutive entries of one row in
+// LDS: NT / 4 16-byte reads at fixed offsets and NT products per 4-element step,
+// instead of 2 NT reads at unpacked addresses.  NT is the smallest that gives
+// every column a lane (ttm4_tiles: ceil(K_b K_c / 16) or one more; 7 for ranks 10).
+//
+// What bounds it is the matrix cores (FP32: 32 NT cycles per 4 elements on each
+// SIMD) as long as a few waves per SIMD are there, so a workgroup keeps little
+// LDS: a bin's rows are not kept (they were: six of 4 KB per bin held a bin to
+// 200 of 1024 elements where slices are short), a slice inside one wave's part
+// goes through one LDS row per wave (STAGE) or straight to Y or its partial
+// slot.  Nothing of the bin is staged either: indices run two rings
+// ahead of their use, factor rows one, as in the three-mode wide kernel,
+// whose order of sums across waves this is too (no atomics, deterministic).
+// 4e5 x 2e5 x 2e4 x 5e3, 2e7 elements, ranks 10: 1.83 / 1.45 / 0.93 / 0.83 ms per mode
+// with the bin's rows in LDS, 1.15 / 1.01 / 0.87 / 0.85 so (0.46 of matrix-core
+// time); BF16 at 5e4 x 601 x 150 x 97, 1e7 elements: 0.46 -> 0.29 ms.
 //
 // BFM (the precision form): the operands are rounded once to BF16 and each
 // block of 16 elements takes NT v_mfma_f32_16x16x16_bf16 per slice present in
 // it (lane group q supplies elements 4q .. 4q+3; other slices' lane groups get
 // a zero A operand), FP32 accumulation, as in the three-mode kernel.
-template <int NT, bool BFM>
+constexpr int TTM4_WAVES = 4;
+// A wave's LDS tile: 16 elements' rows of F_a, F_b and F_c.  The planes of F_b
+// and F_c start 8 and 16 banks on, so that lanes below and above K_b, which
+// read entries of different planes, meet in no bank.
+constexpr int TTM4_FB = 256 + 8, TTM4_FC = 512 + 16, TTM4_TILE = 768 + 16;
+
+// NT for ranks K_b, K_c
+static int ttm4_tiles(int kb, int kc) {
+  for (int nt = (kb * kc + 15) / 16; nt < kc; ++nt) {
+    const int S = nt < 4 ? nt : nt & ~3;
+    const int L = kb <= nt ? 1 : (kb - nt + S - 1) / S + 1;
+    if ((kc - nt) * L <= 16 - kb) return nt;
+  }
+  return kc;
+}
+
+template <int NT, bool BFM, bool STAGE>
 // Up to eight output tiles, at most 170 registers per lane (three waves per
-// SIMD): at ranks 10 the BF16 form would otherwise take 194 (166 + 28
-// accumulation registers) and run at two waves, 26% slower, and the FP32 form
-// drops from 154 to 119.  Wider tiles (a three-wave cap would spill) are held
-// to two waves: left unbounded, 14 to 16 tiles take 250 to 284 registers and
-// run at one wave (ranks 16, four modes: TTM-chain 53 ms against 31 at two).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 8 ? 3 : 2))) void k_ttm4_mfma(
+// SIMD); wider tiles (a three-wave cap would spill) are held to two waves.
+__global__ __launch_bounds__(64 * TTM4_WAVES) __attribute__((amdgpu_waves_per_eu(NT <= 8 ? 3 : 2))) void k_ttm4_mfma(
+    TtmArgs A, int nseg_pad) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int ka = A.Kj[0], kb = A.Kj[1], kc = A.Kj[2], khat = A.khat;
+  const int64_t bin = launch_bin(A);
+  const int64_t e0 = A.bin_ptr[bin];
+  const int E = (int)(A.bin_ptr[bin + 1] - e0);   // multiple of 4
+  const int s0 = A.seg_ptr[bin];
+  const int nseg = A.seg_ptr[bin + 1] - s0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uni(tid >> 6);
+  const int khat4 = (khat + 3) & ~3;
+  int* send = reinterpret_cast<int*>(smem);
+  int* sslot = send + nseg_pad;
+  int* srow = sslot + nseg_pad;
+  float* tile = reinterpret_cast<float*>(srow + nseg_pad) + wave * TTM4_TILE;
+  float* rows = reinterpret_cast<float*>(srow + nseg_pad) + TTM4_WAVES * TTM4_TILE - khat4;   // row w of waves 1 on
+  float* stage = rows + TTM4_WAVES * khat4 + wave * khat4;                // STAGE: one row per wave
+  for (int i = tid; i < nseg; i += 64 * TTM4_WAVES) {
+    send[i] = (int)(A.seg_begin[s0 + i + 1] - e0);
+    sslot[i] = A.seg_slot[s0 + i];
+    srow[i] = A.seg_row[s0 + i];
+  }
+  __syncthreads();
+  const int Q = ((E + 16 * TTM4_WAVES - 1) / (16 * TTM4_WAVES)) * 16;   // elements per wave
+  const int cs = min(wave * Q, E), ce = min(cs + Q, E);
+  const int k = lane >> 4, cix = lane & 15;
+  // this lane's columns: tile t is column (j0 + dj t, q0 + dq t) of (K_b, K_c);
+  // entry `held` of an element's tile rows is the factor kept, entry `run` + t the other
+  constexpr int S = NT < 4 ? NT : NT & ~3;
+  const int L = kb <= NT ? 1 : (kb - NT + S - 1) / S + 1;
+  const bool low = cix < kb;
+  const int place = low ? 0 : (cix - kb) % L, extra = low ? 0 : NT + (cix - kb) / L;
+  const bool there = low || extra < kc;
+  const int held = low ? TTM4_FB + cix : TTM4_FC + (there ? extra : 0);
+  const int run = low ? TTM4_FC : TTM4_FB + S * place;
+  const int t_end = !there ? 0 : low ? NT : place == L - 1 ? min(NT, kb - S * place) : S;   // its tiles in use
+  const int col0 = low ? cix : S * place + kb * extra, dcol = low ? kb : 1;   // column col0 + t dcol
+  floatx4_t C[NT];
+  auto zero = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) C[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  zero();
+  // the destination of segment sg's row, an offset from Y (a select of two
+  // pointers would become a private-memory table)
+  const uintptr_t ybase = reinterpret_cast<uintptr_t>(A.Y);
+  const uintptr_t pdiff = reinterpret_cast<uintptr_t>(A.partial) - ybase;
+  auto row_ptr = [&](int sg) __attribute__((always_inline)) {
+    const int slot = uni(sslot[sg]);
+    const int64_t r64 = slot < 0 ? uni(srow[sg]) : slot;
+    return ybase + (slot < 0 ? 0 : pdiff) + (uintptr_t)(r64 * khat) * 4;
+  };
+  // f(entry offset in the row, register quad, entries of it inside K_a)
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+    if (4 * k >= ka) return;
+    static_for<NT>([&](auto ti) __attribute__((always_inline)) {
+      constexpr int t = decltype(ti)::value;
+      if (t < t_end) f(4 * k + ka * (col0 + t * dcol), C[t], ka - 4 * k);
+    });
+  };
+  // this lane's entries into an LDS row; even K_a in 8-byte words (row offsets
+  // are then even)
+  auto to_lds = [&](float* r, bool add) __attribute__((always_inline)) {
+    if ((ka & 1) == 0) {
+      each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+        float2* w = reinterpret_cast<float2*>(r + o);
+        float2 x = {c[0], c[1]}, y = {c[2], c[3]};
+        if (add) {
+          const float2 p = w[0];
+          x = {p.x + x.x, p.y + x.y};
+        }
+        w[0] = x;
+        if (n > 2) {
+          if (add) {
+            const float2 p = w[1];
+            y = {p.x + y.x, p.y + y.y};
+          }
+          w[1] = y;
+        }
+      });
+    } else {
+      each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < n) r[o + q] = add ? r[o + q] + c[q] : c[q];
+      });
+    }
+  };
+  // an LDS row to its place, 16-byte stores when the row length allows
+  auto row_out = [&](const float* r, uintptr_t rp) __attribute__((always_inline)) {
+    if ((khat & 3) == 0) {
+      const floatx4_t* src = reinterpret_cast<const floatx4_t*>(r);
+      auto* dst = reinterpret_cast<__attribute__((address_space(1))) floatx4_t*>(rp);
+      for (int c4 = lane; c4 < (khat >> 2); c4 += 64) __builtin_nontemporal_store(src[c4], dst + c4);
+    } else {
+      auto* dst = reinterpret_cast<__attribute__((address_space(1))) float*>(rp);
+      for (int c = lane; c < khat; c += 64) __builtin_nontemporal_store(r[c], dst + c);
+    }
+  };
+  const bool vec = (ka & 3) == 0;   // quads are whole and 16-byte aligned
+  int right_row = -1;               // the LDS row of the slice this wave leaves unfinished
+  if (cs < ce) {
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {   // first segment ending after cs
+      const int mid = (lo + hi) >> 1;
+      if (uni(send[mid]) > cs) hi = mid; else lo = mid + 1;
+    }
+    int sg = lo;
+    bool left = sg > 0 ? uni(send[sg - 1]) < cs : cs > 0;
+    int seg_hi = uni(send[sg]);
+    auto flush = [&]() __attribute__((always_inline)) {
+      if (seg_hi > ce) {   // continues into a later wave: stays in C
+        right_row = uni((seg_hi - 1) / Q);
+        return;
+      }
+      if (left) {          // begun by an earlier wave, ends here
+        to_lds(rows + wave * khat4, false);
+      } else {
+        const uintptr_t rp = row_ptr(sg);
+        if constexpr (STAGE) {
+          to_lds(stage, false);
+          wave_lds_sync();
+          row_out(stage, rp);
+          wave_lds_sync();   // the next row's writes follow these reads
+        } else if (vec) {
+          each([&](int o, const floatx4_t& c, int) __attribute__((always_inline)) {
+            __builtin_nontemporal_store(c, reinterpret_cast<__attribute__((address_space(1))) floatx4_t*>(rp + 4 * o));
+          });
+        } else {
+          each([&](int o, const floatx4_t& c, int n) __attribute__((always_inline)) {
+            auto* dst = reinterpret_cast<__attribute__((address_space(1))) float*>(rp + 4 * o);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (q < n) __builtin_nontemporal_store(c[q], dst + q);
+          });
+        }
+      }
+      left = false;
+      zero();
+    };
+    // block g: lane l takes element g + l/4 and 16-byte quarter l%4 of its three
+    // rows (all lanes load: the copies are zero beyond column K).  Reads past
+    // the wave's part are clamped to its last element (their steps are not run).
+    struct Idx { int a, b, c; float v; };
+    struct Blk { u32x4 x, y, z; float v; };
+    const int* la = A.lay[0] + e0;
+    const int* lb = A.lay[1] + e0;
+    const int* lc = A.lay[2] + e0;
+    const float* lv = A.val + e0;
+    // this lane's element of a block in the tile.  BFM: the row turns by its
+    // group of four, so that the four lane groups' rows 4k + u fall in
+    // different banks (a plane row is 16 banks), and a group's writes do too.
+    const int el = lane >> 2;
+    const int trow = BFM ? (el & 12) + ((el + (el >> 2)) & 3) : el;
+    const int tw = 4 * trow + (lane & 3);
+    auto fetch_idx = [&](int g, Idx& r) __attribute__((always_inline)) {
+      const uint32_t e = (uint32_t)min(g + el, ce - 1);
+      r.a = __builtin_nontemporal_load(la + e);
+      r.b = __builtin_nontemporal_load(lb + e);
+      r.c = __builtin_nontemporal_load(lc + e);
+      r.v = __builtin_nontemporal_load(lv + e);
+    };
+    auto fetch = [&](const Idx& i, Blk& r) __attribute__((always_inline)) {
+      const uint32_t o = 4 * (lane & 3);
+      r.x = *reinterpret_cast<const u32x4*>(A.F[0] + ((size_t)(uint32_t)i.a * 16 + o));
+      r.y = *reinterpret_cast<const u32x4*>(A.F[1] + ((size_t)(uint32_t)i.b * 16 + o));
+      r.z = *reinterpret_cast<const u32x4*>(A.F[2] + ((size_t)(uint32_t)i.c * 16 + o));
+      r.v = i.v;
+      asm volatile("" : "+v"(r.v));   // copied now: a copy at the loop's head would wait for the newest loads
+    };
+    // the lane's NT products for the element in row er of the tile
+    auto kron = [&](const float* te, float (&b)[NT]) __attribute__((always_inline)) {
+      const float h = te[held];
+      float f[(NT + 3) & ~3];
+      if constexpr (NT < 4) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) f[t] = te[run + t];
+      } else {
+#pragma unroll
+        for (int t = 0; t < (NT + 3) / 4; ++t) {
+          const float4 x = *reinterpret_cast<const float4*>(te + run + 4 * t);
+          f[4 * t] = x.x; f[4 * t + 1] = x.y; f[4 * t + 2] = x.z; f[4 * t + 3] = x.w;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) b[t] = h * f[t];
+    };
+    auto consume = [&](int g, const Blk& r) __attribute__((always_inline)) {
+      reinterpret_cast<float4*>(tile)[tw] =
+          make_float4(__uint_as_float(r.x.x) * r.v, __uint_as_float(r.x.y) * r.v, __uint_as_float(r.x.z) * r.v,
+                      __uint_as_float(r.x.w) * r.v);
+      reinterpret_cast<u32x4*>(tile + TTM4_FB)[tw] = r.y;
+      reinterpret_cast<u32x4*>(tile + TTM4_FC)[tw] = r.z;
+      wave_lds_sync();
+      if constexpr (!BFM) {
+        float xa[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xa[u] = tile[(4 * u + k) * 16 + cix];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int gu = g + 4 * u;
+          if (gu >= ce) break;
+          if (gu >= seg_hi) {   // a new slice starts at this step
+            flush();
+            ++sg;
+            seg_hi = uni(send[sg]);
+          }
+          float b[NT];
+          kron(tile + (4 * u + k) * 16, b);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) C[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[u], b[t], C[t], 0, 0, 0);
+        }
+      } else {
+        // lane l holds elements 4(l/16) .. +3 of the block
+        const float* tq[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) tq[u] = tile + (4 * k + ((u + k) & 3)) * 16;
+        const bf16x4_t xa = bf16x4_of(tq[0][cix], tq[1][cix], tq[2][cix], tq[3][cix]);
+        float b[4][NT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kron(tq[u], b[u]);
+        bf16x4_t xb[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) xb[t] = bf16x4_of(b[0][t], b[1][t], b[2][t], b[3][t]);
+        const bf16x4_t zero4 = {0, 0, 0, 0};
+        int q0 = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int gq = g + 4 * q;
+          if (gq >= ce) break;
+          if (gq >= seg_hi) {   // quad q starts a new slice: close the run before it
+            if (q > q0) {
+              const bf16x4_t a = k >= q0 && k < q ? xa : zero4;
+#pragma unroll
+              for (int t = 0; t < NT; ++t) C[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, xb[t], C[t], 0, 0, 0);
+            }
+            flush();
+            ++sg;
+            seg_hi = uni(send[sg]);
+            q0 = q;
+          }
+        }
+        const int qend = min(4, (ce - g) >> 2);
+        if (qend > q0) {
+          const bf16x4_t a = k >= q0 && k < qend ? xa : zero4;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) C[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, xb[t], C[t], 0, 0, 0);
+        }
+      }
+      wave_lds_sync();   // the next block's write follows these reads
+    };
+    // indices run a ring ahead of the rows; every refill is unconditional and
+    // kept in issue order, so the wait before each block is for its own loads
+    static_assert(TTM4_RING == 3, "the ring steps below are written out for three blocks");
+    Idx ix[TTM4_RING];
+    Blk ring[TTM4_RING];
+#pragma unroll
+    for (int d = 0; d < TTM4_RING; ++d) fetch_idx(cs + 16 * d, ix[d]);
+#pragma unroll
+    for (int d = 0; d < TTM4_RING; ++d) {
+      fetch(ix[d], ring[d]);
+      fetch_idx(cs + 16 * (TTM4_RING + d), ix[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // (static_for: with many tiles the compiler would leave the ring a loop, in memory)
+    for (int g = cs; g < ce; g += 16 * TTM4_RING) {
+      static_for<TTM4_RING>([&](auto di) __attribute__((always_inline)) {
+        constexpr int d = decltype(di)::value;
+        const int gg = g + 16 * d;
+        if (gg < ce) consume(gg, ring[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(ix[d], ring[d]);
+        fetch_idx(gg + 32 * TTM4_RING, ix[d]);
+      });
+    }
+    flush();
+  }
+  __syncthreads();
+  // pieces of slices that a later wave ended, added in wave order
+#pragma unroll 1
+  for (int w = 0; w + 1 < TTM4_WAVES; ++w) {
+    if (wave == w && right_row >= 0) to_lds(rows + right_row * khat4, true);
+    __syncthreads();
+  }
+  if (cs > 0 && cs < ce) {   // the slice begun by an earlier wave that ended here
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (uni(send[mid]) > cs) hi = mid; else lo = mid + 1;
+    }
+    const bool left = lo > 0 ? uni(send[lo - 1]) < cs : true;
+    if (left && uni(send[lo]) <= ce) row_out(rows + wave * khat4, row_ptr(lo));
+  }
+}
+
+// The four-mode step for one or two output tiles (K_b K_c at most 32).  So little
+// matrix-core time does not cover reading indices in blocks of 16; here the
+// bin's coordinates, values and rows are kept in LDS (the rows are short), as
+// in the one-wave three-mode kernel, and a lane takes column 16t + cix of the
+// Kronecker row, two reads and a product each.  A wave's slices that continue
+// into a neighbouring wave keep their partial rows in registers and are added to
+// the bin's LDS rows in wave order after the main loop (no atomics,
+// deterministic).  4e5 x 2e5 x 2e4 x 5e3, 8e6 elements, ranks 4: 0.85 ms for the four
+// chains here, 0.94 with k_ttm4_mfma; with three tiles that one is as fast.
+template <int NT, bool BFM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ttm4_rows_mfma(
     TtmArgs A, int Epad, int nseg_pad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int ka = A.Kj[0], kb = A.Kj[1], kbc = A.Kj[1] * A.Kj[2];
@@ -1064,15 +1397,26 @@ bool ttm_uses_mfma4(int N, const int32_t* K, int n, const int* kp) {
   return true;
 }
 
-// Columns of Y a bin keeps in LDS per launch: whole rows for the matrix-core
-// kernels, one tile of TTMV_TILE columns for the vector-ALU kernel.
+// Mode n of a four-mode tensor takes k_ttm4_rows_mfma: one or two output tiles.
+static bool ttm4_keeps_rows(const int32_t* K, int n) {
+  int k[3], no = 0;
+  for (int j = 0; j < 4; ++j)
+    if (j != n) k[no++] = K[j];
+  return k[1] * k[2] <= 32;
+}
+
+// Columns of Y a bin keeps in LDS per launch: whole rows for the one-wave
+// three-mode kernel and the four-mode kernel of one or two tiles, one tile of
+// TTMV_TILE columns for the vector-ALU kernel.  k_ttm4_mfma keeps none of the
+// bin's rows and goes by the vector-ALU kernel's, which may run on its bins.
 int ttm_tile_width(int N, const int32_t* K, int n) {
   int kp16[8];
   for (int j = 0; j < N; ++j) kp16[j] = K[j] <= 16 ? 16 : 0;
   int kh = 1;
   for (int j = 0; j < N; ++j)
     if (j != n) kh *= K[j];
-  if (ttm_uses_mfma(N, K, n, kp16) || ttm_uses_mfma4(N, K, n, kp16)) return kh;
+  if (ttm_uses_mfma(N, K, n, kp16)) return kh;
+  if (ttm_uses_mfma4(N, K, n, kp16)) return ttm4_keeps_rows(K, n) ? kh : std::min(kh, TTMV_TILE);
   return TTMV_TILE;
 }
 
@@ -1092,9 +1436,8 @@ int64_t ttm_default_bin_nnz(int N, const int32_t* K, int n, int kernel) {
 
 int ttm_rows_cap(Ctx* c, int64_t tile_w) {
   // LDS budget for a bin's rows: about 40 KB so three bins share a CU, never
-  // past the hardware limit.  Wide rows (the four-mode matrix-core kernel,
-  // Khat >= 512) leave room for that kernel's staging (16 bytes per element)
-  // and tiles (12 KB): 24 KB of rows keep three of its bins on a CU.
+  // past the hardware limit.  Wide rows (k_ttm4_rows_mfma, Khat >= 512) leave
+  // room for that kernel's staging (16 bytes per element) and tiles (12 KB).
   int64_t budget = tile_w >= 512 ? 24576 : 40960;
   if ((int64_t)c->lds_per_block < budget) budget = (int64_t)c->lds_per_block;
   int64_t cap = budget / (4 * tile_w + 4);
@@ -1200,25 +1543,45 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
   } else if (!vector_only && ttm_uses_mfma3w(N, K, n, kp)) {
     ttm3w_launch(c, pl, a);
   } else if (!vector_only && ttm_uses_mfma4(N, K, n, kp)) {
-    const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
     const int nseg_pad = (int)((pl.R_max + 3) & ~(int64_t)3);
-    const size_t lds = 3 * sizeof(int) * (size_t)nseg_pad + 16 * (size_t)Epad + sizeof(float) * 4 * 768 +
-                       sizeof(float) * (size_t)pl.R_max * (size_t)pl.khat;
+    const dim3 g((unsigned)pl.P), b(64 * TTM4_WAVES);
+    if (ttm4_keeps_rows(K, n)) {
+      const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
+      const size_t lds = 3 * sizeof(int) * (size_t)nseg_pad + 16 * (size_t)Epad + sizeof(float) * 4 * 768 +
+                         sizeof(float) * (size_t)pl.R_max * (size_t)pl.khat;
+      TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
+      auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, c->stream, a, Epad, nseg_pad); };
+      if (a.Kj[1] * a.Kj[2] <= 16)
+        bf16 ? go(k_ttm4_rows_mfma<1, true>) : go(k_ttm4_rows_mfma<1, false>);
+      else
+        bf16 ? go(k_ttm4_rows_mfma<2, true>) : go(k_ttm4_rows_mfma<2, false>);
+    } else {
+    const size_t row = sizeof(float) * (((size_t)pl.khat + 3) & ~(size_t)3);
+    const size_t base = 3 * sizeof(int) * (size_t)nseg_pad + sizeof(float) * TTM4_WAVES * TTM4_TILE + (TTM4_WAVES - 1) * row;
+    // Rows staged while three bins still share a CU; longer ones (Khat above
+    // about 1300) go straight from the accumulators: the row would cost a wave
+    // per SIMD (ranks 16: 1.48 ms for four chains of 1e6 elements, 2.76 with the
+    // bin's rows kept)
+    const bool stage = 3 * (base + TTM4_WAVES * row) <= c->lds_per_block;
+    const size_t lds = stage ? base + TTM4_WAVES * row : base;
     TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
-    const dim3 g((unsigned)pl.P), b(256);
-    switch ((a.Kj[1] * a.Kj[2] + 15) / 16) {
-#define TK_TTM4_CASE(NT)                                                                         \
-      case NT:                                                                                   \
-        if (bf16)                                                                                \
-          hipLaunchKernelGGL((k_ttm4_mfma<NT, true>), g, b, lds, c->stream, a, Epad, nseg_pad);  \
-        else                                                                                     \
-          hipLaunchKernelGGL((k_ttm4_mfma<NT, false>), g, b, lds, c->stream, a, Epad, nseg_pad); \
+    auto go = [&](auto direct, auto staged) {
+      hipLaunchKernelGGL((stage ? staged : direct), g, b, lds, c->stream, a, nseg_pad);
+    };
+    switch (ttm4_tiles(a.Kj[1], a.Kj[2])) {
+#define TK_TTM4_CASE(NT)                                                        \
+      case NT:                                                                  \
+        if (bf16)                                                               \
+          go(k_ttm4_mfma<NT, true, false>, k_ttm4_mfma<NT, true, true>);        \
+        else                                                                    \
+          go(k_ttm4_mfma<NT, false, false>, k_ttm4_mfma<NT, false, true>);      \
         break;
-      TK_TTM4_CASE(1) TK_TTM4_CASE(2) TK_TTM4_CASE(3) TK_TTM4_CASE(4) TK_TTM4_CASE(5) TK_TTM4_CASE(6)
+      TK_TTM4_CASE(3) TK_TTM4_CASE(4) TK_TTM4_CASE(5) TK_TTM4_CASE(6)
       TK_TTM4_CASE(7) TK_TTM4_CASE(8) TK_TTM4_CASE(9) TK_TTM4_CASE(10) TK_TTM4_CASE(11) TK_TTM4_CASE(12)
       TK_TTM4_CASE(13) TK_TTM4_CASE(14) TK_TTM4_CASE(15) TK_TTM4_CASE(16)
 #undef TK_TTM4_CASE
       default: fail(TK_ERR_UNSUPPORTED, "four-mode TTM: rank above 16");
+    }
     }
     TK_CHECK_LAUNCH();
   } else {
