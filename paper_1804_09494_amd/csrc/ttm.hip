@@ -1309,33 +1309,35 @@ __device__ __forceinline__ float fix_sum(const float* __restrict__ buf, int a, i
   }
   return s;
 }
-// One wave per run of rows (four runs per workgroup): lane l sums columns
-// l, l + 64, ... of rows [a, b) of buf in row order into out; with khat a
-// multiple of 4, four columns per lane through 16-byte loads.  Each column's
-// adds keep fix_sum's order, so the result does not depend on the form.
+// One wave per run of rows and share of the columns (four runs per workgroup,
+// shares along the grid's y): rows [a, b) of buf in row order into out; with khat
+// a multiple of 4, four columns per lane through 16-byte loads.  Each column's
+// adds keep fix_sum's order, so the result does not depend on the form.  A run
+// is a chain of batches of loads in flight: with one wave for all columns and
+// batches of 8, runs of 128 rows of 1000 columns took 58 us, so 15.
 __device__ __forceinline__ void fix_sum_wave(const float* __restrict__ buf, int a, int b, int khat,
                                              float* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
+  const int lane = (threadIdx.x & 63) + 64 * blockIdx.y, step = 64 * gridDim.y;
   if ((khat & 3) == 0) {
     const int kq = khat >> 2;
-    for (int c4 = lane; c4 < kq; c4 += 64) {
+    for (int c4 = lane; c4 < kq; c4 += step) {
       floatx4_t s = {0.f, 0.f, 0.f, 0.f};
-      for (int a0 = a; a0 < b; a0 += 8) {
-        floatx4_t v[8];
+      for (int a0 = a; a0 < b; a0 += 16) {
+        floatx4_t v[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          v[i] = a0 + i < b ? reinterpret_cast<const floatx4_t*>(buf + (int64_t)(a0 + i) * khat)[c4]
-                            : floatx4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 16; ++i)   // past the run: its last row again, not added
+          v[i] = reinterpret_cast<const floatx4_t*>(buf + (int64_t)min(a0 + i, b - 1) * khat)[c4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 16; ++i)
           if (a0 + i < b) s += v[i];
       }
       reinterpret_cast<floatx4_t*>(out)[c4] = s;
     }
   } else {
-    for (int c = lane; c < khat; c += 64) out[c] = fix_sum(buf, a, b, khat, c);
+    for (int c = lane; c < khat; c += step) out[c] = fix_sum(buf, a, b, khat, c);
   }
 }
+static unsigned fix_shares(int64_t khat) { return (unsigned)ceil_div(khat, (khat & 3) == 0 ? 256 : 64); }
 constexpr int FIX_WAVES = 4;   // runs per workgroup
 __global__ __launch_bounds__(64 * FIX_WAVES) void k_fixup_level(const int32_t* __restrict__ lo,
                                                                 const int32_t* __restrict__ hi, int64_t first,
@@ -1602,13 +1604,15 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
     int64_t first = pl.n_slots, off = 0;
     for (int64_t nl : pl.fix_n) {
       const int32_t* lohi = pl.fix_lohi.as<int32_t>() + off;
-      hipLaunchKernelGGL(k_fixup_level, dim3((unsigned)ceil_div(nl, FIX_WAVES)), dim3(64 * FIX_WAVES), 0, c->stream,
+      hipLaunchKernelGGL(k_fixup_level, dim3((unsigned)ceil_div(nl, FIX_WAVES), fix_shares(pl.khat)),
+                         dim3(64 * FIX_WAVES), 0, c->stream,
                          lohi, lohi + nl, first, nl, buf, (int)pl.khat);
       TK_CHECK_LAUNCH();
       first += nl;
       off += 2 * nl;
     }
-    hipLaunchKernelGGL(k_fixup, dim3((unsigned)ceil_div(pl.n_bad, FIX_WAVES)), dim3(64 * FIX_WAVES), 0, c->stream,
+    hipLaunchKernelGGL(k_fixup, dim3((unsigned)ceil_div(pl.n_bad, FIX_WAVES), fix_shares(pl.khat)),
+                       dim3(64 * FIX_WAVES), 0, c->stream,
                        pl.bad_row.as<int32_t>(),
                        pl.fix_fin.as<int32_t>(), pl.n_bad, buf, (int)pl.khat, Y);
     TK_CHECK_LAUNCH();
