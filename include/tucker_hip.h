@@ -162,7 +162,10 @@ const char* tk_status_string(tk_status s);
 const char* tk_last_error(const tk_ctx* ctx);
 tk_status tk_default_options(tk_options* out);
 tk_status tk_set_options(tk_ctx* ctx, const tk_options* opt);
-/* Change the stream later calls are ordered on. */
+/* Change the stream later calls are ordered on.  The call does not wait, so it may be made while a
+ * graph is captured.  Work still queued on the former stream keeps what it reads: the next call that
+ * allocates or releases device memory waits for the device first.  Calls that only launch work share
+ * the context's buffers (factors, partial rows) with it; the caller orders the two streams for those. */
 tk_status tk_set_stream(tk_ctx* ctx, void* hip_stream);
 
 /* ---- tensor (Section 3: the element list E) --------------------------------------------------- */

@@ -44,23 +44,13 @@ void* Ctx::alloc_raw(size_t bytes, size_t* cap) {
     p = allocator.alloc(bytes, allocator.user);
     if (!p) fail(TK_ERR_OOM, "the allocator hook returned no memory for " + std::to_string(bytes) + " bytes");
   } else {
-    if (caches()) {
-      *cap = BlockCache::round_up(bytes);
-      p = cache.take(*cap, stream, cap);
+    if (caches())
+      p = cache.alloc(bytes, cap);
+    else if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      p = nullptr;
     }
-    if (!p) {
-      hipError_t e = hipMalloc(&p, *cap);
-      if (e != hipSuccess && !cache.blocks.empty()) {   // give back what is kept, then once more
-        (void)hipGetLastError();
-        cache.trim(0, 0);
-        *cap = bytes;
-        e = hipMalloc(&p, *cap);
-      }
-      if (e != hipSuccess || !p) {
-        (void)hipGetLastError();
-        fail(TK_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-      }
-    }
+    if (!p) fail(TK_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
   }
   bytes_in_use += (int64_t)bytes;
   return p;
@@ -71,7 +61,7 @@ void Ctx::free_raw(void* p, size_t bytes, size_t cap) {
     if (allocator.free)
       allocator.free(p, bytes, allocator.user);
     else if (caches())
-      cache.give(p, cap, stream);
+      cache.free(p, cap);
     else
       (void)hipFree(p);
     bytes_in_use -= (int64_t)bytes;
@@ -329,6 +319,7 @@ tk_status tk_create(int device, void* hip_stream, const tk_allocator* allocator,
   tk_status s = guard(c, [&] {
     TK_HIP(hipSetDevice(device));
     c->device = device;
+    c->cache.set_device(device);
     if (allocator) c->allocator = *allocator;
     noalloc_scratch_init(device);
     c->stream = (hipStream_t)hip_stream;
@@ -367,13 +358,14 @@ tk_status tk_set_options(tk_ctx* c, const tk_options* o) {
     TK_REQUIRE(o->ttm_kernel >= TK_TTM_AUTO && o->ttm_kernel <= TK_TTM_FIBER, TK_ERR_INVALID_ARG, "ttm_kernel");
     TK_REQUIRE(o->eig_method >= TK_EIG_AUTO && o->eig_method <= TK_EIG_MATFREE, TK_ERR_INVALID_ARG, "eig_method");
     c->opt = *o;
-    if (!c->caches()) c->cache.trim(0, 0);
+    if (!c->caches()) c->cache.release();
   });
 }
 
 tk_status tk_set_stream(tk_ctx* c, void* s) {
   if (!c) return TK_ERR_INVALID_ARG;
   c->stream = (hipStream_t)s;
+  c->cache.stream_changed();
   return TK_OK;
 }
 

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/tucker_hip.h"
+#include "block_cache.hpp"
 
 namespace tk {
 
@@ -80,62 +81,6 @@ class Buf {
   void* p_ = nullptr;
   size_t bytes_ = 0;
   size_t cap_ = 0;   // size of the block behind it
-};
-
-// Device blocks a context has let go of and keeps for its next allocations: a
-// load and partition of 2e7 elements makes 195 allocations, and hipMalloc and
-// hipFree (which also waits for the device) took three quarters of its time.
-// A block is handed out again only on the stream it was let go on, so work
-// still queued there comes first; others go back to the runtime.  At most
-// MAX_BYTES are kept (blocks above half of that never), all of it is given back
-// when an allocation fails and when the context ends.  Contexts with an
-// allocator hook or a memory limit keep nothing.
-struct BlockCache {
-  static constexpr size_t MAX_BYTES = (size_t)4 << 30;
-  static constexpr size_t MAX_BLOCKS = 1024;
-  struct Block {
-    void* p;
-    size_t cap;
-    hipStream_t stream;
-  };
-  std::vector<Block> blocks;   // oldest first
-  size_t bytes = 0;
-  ~BlockCache() { trim(0, 0); }
-  static size_t round_up(size_t n) {
-    const size_t q = n < ((size_t)1 << 20) ? 4096 : (size_t)1 << 20;
-    return (n + q - 1) / q * q;
-  }
-  // the smallest block of at least `want` bytes, at most a quarter larger
-  void* take(size_t want, hipStream_t stream, size_t* cap) {
-    size_t best = blocks.size();
-    for (size_t i = 0; i < blocks.size(); ++i)
-      if (blocks[i].stream == stream && blocks[i].cap >= want && blocks[i].cap - want <= want / 4 + 65536 &&
-          (best == blocks.size() || blocks[i].cap < blocks[best].cap))
-        best = i;
-    if (best == blocks.size()) return nullptr;
-    void* p = blocks[best].p;
-    *cap = blocks[best].cap;
-    bytes -= blocks[best].cap;
-    blocks.erase(blocks.begin() + (std::ptrdiff_t)best);
-    return p;
-  }
-  void give(void* p, size_t cap, hipStream_t stream) {
-    if (cap > MAX_BYTES / 2) {
-      (void)hipFree(p);
-      return;
-    }
-    blocks.push_back({p, cap, stream});
-    bytes += cap;
-    trim(MAX_BYTES, MAX_BLOCKS);
-  }
-  void trim(size_t max_bytes, size_t max_blocks) {
-    size_t n = 0;
-    while (n < blocks.size() && (bytes > max_bytes || blocks.size() - n > max_blocks)) {
-      (void)hipFree(blocks[n].p);
-      bytes -= blocks[n++].cap;
-    }
-    blocks.erase(blocks.begin(), blocks.begin() + (std::ptrdiff_t)n);
-  }
 };
 
 // Per-mode plan: the Lite partition, the mode-sorted copy of the tensor and

@@ -1,7 +1,7 @@
 // Device-wide sort / scan / reduce primitives (rocPRIM), wrapped with the
 // context's allocator for their temporary storage (let go while the work is
-// queued: the context hands a block out again on the same stream only).  Used by the set-up
-// stages (coalescing and the Lite partition), never by the TTM-chain.
+// queued: the context's next work comes after it on the stream).  Used by the
+// set-up stages (coalescing and the Lite partition), never by the TTM-chain.
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_reduce.hpp>
 #include <rocprim/device/device_scan.hpp>
