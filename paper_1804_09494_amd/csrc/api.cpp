@@ -314,9 +314,10 @@ tk_status tk_create(int device, void* hip_stream, const tk_allocator* allocator,
     return TK_ERR_DEVICE;
   }
   if (device < 0 || device >= ndev) return TK_ERR_INVALID_ARG;
-  tk_ctx* c = new (std::nothrow) tk_ctx();
-  if (!c) return TK_ERR_OOM;
-  tk_status s = guard(c, [&] {
+  tk_ctx* c = nullptr;
+  tk_status s = guard(c, [&] { c = new tk_ctx(); });
+  if (s != TK_OK) return s;
+  s = guard(c, [&] {
     TK_HIP(hipSetDevice(device));
     c->device = device;
     c->cache.set_device(device);

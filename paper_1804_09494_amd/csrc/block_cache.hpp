@@ -26,7 +26,8 @@ class BlockCache {
   static constexpr size_t MAX_BYTES = (size_t)4 << 30;
   static constexpr size_t MAX_BLOCKS = 1024;
 
-  BlockCache() = default;
+  // room for one block more than are kept: blocks are released in destructors, which must not throw
+  BlockCache() { blocks_.reserve(MAX_BLOCKS + 1); }
   BlockCache(const BlockCache&) = delete;
   BlockCache& operator=(const BlockCache&) = delete;
   ~BlockCache() { release(); }

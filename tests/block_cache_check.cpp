@@ -4,6 +4,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 
 #include "block_cache.hpp"
 
@@ -12,6 +13,7 @@ std::map<void*, size_t> live;   // blocks the runtime has handed out
 size_t room = (size_t)1 << 60;  // bytes it still has
 int mallocs = 0, frees = 0, waits = 0;
 bool capturing = false;
+bool host_full = false;         // host allocations throw
 
 void check(bool ok, const char* what) {
   if (ok) return;
@@ -19,6 +21,14 @@ void check(bool ok, const char* what) {
   std::exit(1);
 }
 }  // namespace
+
+void* operator new(size_t n) {
+  if (host_full) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
@@ -90,6 +100,17 @@ int main(int argc, char** argv) {
     capturing = false;
     check(c.alloc(10 * MB, &cap) == p && waits == 1, "waited for once the capture is over");
     c.free(p, cap);
+  } else if (!std::strcmp(name, "release_without_host_memory")) {
+    // a release runs in destructors: it may not throw, and the count stays bounded
+    BlockCache c;
+    static void* p[1200];
+    static size_t n[1200];
+    for (int i = 0; i < 1200; ++i) p[i] = c.alloc(4096, &n[i]);
+    // (the stand-in's own records of frees do not allocate)
+    host_full = true;
+    for (int i = 0; i < 1200; ++i) c.free(p[i], n[i]);
+    host_full = false;
+    check(live.size() == BlockCache::MAX_BLOCKS, "at most MAX_BLOCKS are kept");
   } else {
     std::fprintf(stderr, "no check of this name\n");
     return 2;

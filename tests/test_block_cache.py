@@ -6,7 +6,7 @@ import pytest
 
 from tests.conftest import ROOT
 
-CHECKS = ["reuse", "stream_change", "stream_change_in_capture"]
+CHECKS = ["reuse", "stream_change", "stream_change_in_capture", "release_without_host_memory"]
 
 
 @pytest.fixture(scope="module")
