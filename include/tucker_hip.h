@@ -154,7 +154,12 @@ typedef struct {
 
 /* Create a context on HIP device `device`; `hip_stream` is a hipStream_t or
  * NULL; `allocator` (copied; may be NULL = hipMalloc / hipFree) backs every
- * device allocation the context makes. */
+ * device allocation the context makes.
+ * Without an allocator and without mem_limit_bytes a context keeps up to 4 GiB
+ * of device memory it has released for its next allocations.  It goes back to
+ * the runtime in tk_destroy, when an allocation of any context on that device
+ * fails, and when tk_set_options sets a memory limit (which may be taken off
+ * again at once). */
 tk_status tk_create(int device, void* hip_stream, const tk_allocator* allocator, tk_ctx** out);
 void tk_destroy(tk_ctx* ctx);
 const char* tk_status_string(tk_status s);

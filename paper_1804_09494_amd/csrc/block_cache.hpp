@@ -4,7 +4,9 @@
 // Contexts with an allocator hook or a memory limit do not use it.
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
+#include <mutex>
 #include <vector>
 
 #include <hip/hip_runtime_api.h>
@@ -19,34 +21,44 @@ namespace tk {
 // in use on the present stream only.  tk_set_stream itself does not wait: it
 // may be called while a graph is captured, where a wait is an error.
 //
-// At most MAX_BYTES are kept (blocks above half of that never), all of it is
-// given back when an allocation fails and when the context ends.
+// At most MAX_BYTES are kept (blocks above half of that never).  All of it is
+// given back when the context ends, and when an allocation of any context of
+// the process fails on the same device.  Only that call touches another
+// context's cache, hence the lock; hipFree waits for work that still uses a block.
 class BlockCache {
  public:
   static constexpr size_t MAX_BYTES = (size_t)4 << 30;
   static constexpr size_t MAX_BLOCKS = 1024;
 
   // room for one block more than are kept: blocks are released in destructors, which must not throw
-  BlockCache() { blocks_.reserve(MAX_BLOCKS + 1); }
+  BlockCache() {
+    blocks_.reserve(MAX_BLOCKS + 1);
+    Caches& a = caches();
+    std::lock_guard<std::mutex> lock(a.mu);
+    a.list.push_back(this);
+  }
   BlockCache(const BlockCache&) = delete;
   BlockCache& operator=(const BlockCache&) = delete;
-  ~BlockCache() { release(); }
+  ~BlockCache() {
+    {
+      Caches& a = caches();
+      std::lock_guard<std::mutex> lock(a.mu);
+      a.list.erase(std::find(a.list.begin(), a.list.end(), this));
+    }
+    release();
+  }
 
   void set_device(int device) { device_ = device; }
 
   // A block of at least `bytes` (*cap: its size), or null when the device has none.
   void* alloc(size_t bytes, size_t* cap) {
     *cap = round_up(bytes);
-    void* p = blocks_.empty() || !settle() ? nullptr : take(*cap, cap);
-    if (p) return p;
-    if (hipMalloc(&p, *cap) == hipSuccess && p) return p;
-    (void)hipGetLastError();
-    if (blocks_.empty()) return nullptr;
-    release();   // give back what is kept, then once more
-    *cap = bytes;
-    if (hipMalloc(&p, *cap) == hipSuccess && p) return p;
-    (void)hipGetLastError();
-    return nullptr;
+    void* p = settle() ? take(*cap, cap) : nullptr;
+    if (p || (p = from_runtime(*cap))) return p;
+    *cap = bytes;   // no more than asked for, what every context keeps given back
+    if ((p = from_runtime(bytes))) return p;
+    release_all(device_);
+    return from_runtime(bytes);
   }
 
   void free(void* p, size_t cap) {
@@ -54,6 +66,7 @@ class BlockCache {
       (void)hipFree(p);
       return;
     }
+    std::lock_guard<std::mutex> lock(mu_);
     blocks_.push_back({p, cap});
     bytes_ += cap;
     trim(MAX_BYTES, MAX_BLOCKS);
@@ -62,7 +75,10 @@ class BlockCache {
   // Work queued so far is on another stream than the work to come.
   void stream_changed() { moved_ = true; }
 
-  void release() { trim(0, 0); }
+  void release() {
+    std::lock_guard<std::mutex> lock(mu_);
+    trim(0, 0);
+  }
 
  private:
   struct Block {
@@ -73,6 +89,28 @@ class BlockCache {
   static size_t round_up(size_t n) {
     const size_t q = n < ((size_t)1 << 20) ? 4096 : (size_t)1 << 20;
     return (n + q - 1) / q * q;
+  }
+
+  struct Caches {
+    std::mutex mu;
+    std::vector<BlockCache*> list;
+  };
+  static Caches& caches() {
+    static Caches* a = new Caches;   // outlives contexts that end with the process
+    return *a;
+  }
+  static void release_all(int device) {
+    Caches& a = caches();
+    std::lock_guard<std::mutex> lock(a.mu);
+    for (BlockCache* c : a.list)
+      if (c->device_ == device) c->release();
+  }
+
+  static void* from_runtime(size_t n) {
+    void* p = nullptr;
+    if (hipMalloc(&p, n) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
   }
 
   // False when the device cannot be waited for (a capture is under way).
@@ -90,6 +128,7 @@ class BlockCache {
 
   // the smallest block of at least `want` bytes, at most a quarter larger
   void* take(size_t want, size_t* cap) {
+    std::lock_guard<std::mutex> lock(mu_);
     size_t best = blocks_.size();
     for (size_t i = 0; i < blocks_.size(); ++i)
       if (blocks_[i].cap >= want && blocks_[i].cap - want <= want / 4 + 65536 &&
@@ -112,6 +151,7 @@ class BlockCache {
     blocks_.erase(blocks_.begin(), blocks_.begin() + (std::ptrdiff_t)n);
   }
 
+  std::mutex mu_;               // blocks_ and bytes_
   std::vector<Block> blocks_;   // oldest first
   size_t bytes_ = 0;
   int device_ = 0;

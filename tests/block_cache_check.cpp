@@ -111,6 +111,28 @@ int main(int argc, char** argv) {
     for (int i = 0; i < 1200; ++i) c.free(p[i], n[i]);
     host_full = false;
     check(live.size() == BlockCache::MAX_BLOCKS, "at most MAX_BLOCKS are kept");
+  } else if (!std::strcmp(name, "other_context")) {
+    // an allocation that fails gets back what the device's other contexts keep
+    BlockCache a, b, far;
+    far.set_device(1);
+    void* p = a.alloc(10 * MB, &cap);
+    void* f = far.alloc(10 * MB, &cap2);
+    a.free(p, cap);
+    far.free(f, cap2);
+    room = 0;
+    p = b.alloc(10 * MB, &cap);
+    check(p != nullptr, "the other context's block was given back");
+    check(frees == 1, "another device's blocks stay");
+    check(b.alloc(1, &cap2) == nullptr, "nothing left: null");
+    room = (size_t)1 << 60;
+    b.free(p, cap);
+  } else if (!std::strcmp(name, "exact_size")) {
+    // sizes are rounded up; where only the size asked for is there, it is enough
+    BlockCache c;
+    room = 2 * MB + 1;
+    void* p = c.alloc(2 * MB + 1, &cap);
+    check(p && cap == 2 * MB + 1, "no more than asked for");
+    c.free(p, cap);
   } else {
     std::fprintf(stderr, "no check of this name\n");
     return 2;

@@ -6,7 +6,8 @@ import pytest
 
 from tests.conftest import ROOT
 
-CHECKS = ["reuse", "stream_change", "stream_change_in_capture", "release_without_host_memory"]
+CHECKS = ["reuse", "stream_change", "stream_change_in_capture", "release_without_host_memory",
+          "other_context", "exact_size"]
 
 
 @pytest.fixture(scope="module")
