@@ -305,6 +305,9 @@ __global__ __launch_bounds__(64 * EVAL_WAVES) void k_eval3(EvalArgs A, float* __
         const float* fc = A.Fc + (int64_t)A.row_slice[A.seg_row[msg]] * 16;
         M = floatx4_e{0.f, 0.f, 0.f, 0.f};
         for (int c = 0; c < A.Kc; ++c) M += Gs[64 * c + lane] * fc[c];
+        // entries beyond K_a and K_b are zero whatever F_c holds (0 times an infinity is not)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) M[s] = i16 < A.Kb && 4 * q + s < A.Ka ? M[s] : 0.f;
       }
       floatx4_e D = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
