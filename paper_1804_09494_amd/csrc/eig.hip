@@ -485,13 +485,15 @@ __global__ __launch_bounds__(EIG_THREADS) void k_syev_topk(const double* __restr
 //   2. Eigenvalues by multisection on the Sturm sequence of the leading
 //      principal minors, p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: two
 //      multiply-adds per step and no division.  T is scaled by a power of two to
-//      norm [1, 2) and e^2 floored at 1e-30 (a perturbation below 1e-15 of the
+//      norm [1, 2) and e^2 floored at 1e-36 (a perturbation below 1e-18 of the
 //      norm), so that eight steps cannot underflow (each shrinks the pair
 //      (p_i, p_{i-1}) by at most e^2 / 6); the pair is rescaled every eighth step.
+//      How far it goes: see small_is_fine.
 //   3. Inverse iteration, lane j of one row of 16 for vector j.  What it needs is
 //      all the LDS holds beside the packed reflectors, so n up to 128 runs here.
 //   4. Back-transformation, a row of 16 lanes per vector, and, where
-//      eigenvalues are close, modified Gram-Schmidt over the rows, twice.
+//      eigenvalues are close (fine: always), modified Gram-Schmidt over the
+//      rows, twice.
 //
 // Measured at n = 100, K = 10 (one launch): 354 -> 161 us against a form with the
 // matrix in LDS, eight waves, whose passes were bound by LDS reads (three
@@ -534,6 +536,15 @@ static SmallLayout small_layout(int n) {
   return L;
 }
 
+// Up to n (n + 6 K) = 16640 (n = 102 at K = 10, 89 at K = 16) an eigenvalue stops
+// at 1e-11 of the norm: inverse iteration needs no more, the SVD step's
+// CholeskyQR2 restores what is left in U, and the eigenvalues only scale its
+// columns.  Larger problems are taken to FP64
+// resolution as in the general solver: the Rayleigh-Ritz steps of the block-Krylov solver
+// for ranks from 12 on are among them, and an eigenvalue's error there is a
+// floor of the residual that a caller's eig_tol is compared with.
+static bool small_is_fine(int n, int K) { return n * (n + 6 * K) > 16640; }
+
 // Newton-refined hardware reciprocal
 __device__ __forceinline__ double rcp2(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -551,7 +562,7 @@ __device__ __forceinline__ double col_of(const double (&x)[NC], int J) {
 // NG: 16-row groups of the matrix (n <= 16 NG).
 template <int NG>
 __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restrict__ G, int n, int K, int Kout,
-                                                           SmallLayout L, double* __restrict__ lam_out,
+                                                           bool fine, SmallLayout L, double* __restrict__ lam_out,
                                                            double* __restrict__ VK) {
   extern __shared__ __align__(16) double sh[];
   constexpr int NC = NG <= 4 ? 1 : 2;     // columns per lane, and row-layout registers
@@ -778,8 +789,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
   for (int i = tid; i < 16 * n; i += SM_THREADS) Z[i] = start_entry(i & 15, i >> 4);
   __syncthreads();
 
-  // 2. multisection until the interval is below 1e-11 of the norm: inverse
-  // iteration needs no more, and the eigenvalues only scale U's columns
+  // 2. multisection until the interval is below 1e-11 of the norm (fine: at
+  // FP64's resolution)
   {
     // eigenvalues below x: sign changes of the sequence
     auto count = [&](double xp) __attribute__((always_inline)) {
@@ -799,7 +810,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
       };
       for (int i0 = 0; i0 < n; i0 += 16) {
         const double dr = d[i0 + l16], er = i0 + l16 > 0 ? e[i0 + l16 - 1] : 0.0;
-        const double e2r = fmax(er * er, 1e-30);
+        const double e2r = fmax(er * er, 1e-36);
         if (i0 + 16 <= n) {
           static_for<16>([&](auto ii) __attribute__((always_inline)) {
             constexpr int i = decltype(ii)::value;
@@ -824,7 +835,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
     const int MS = K <= 4 ? 64 : K <= 8 ? 32 : 16;   // lanes per eigenvalue, one point each
     const int g = tid / MS, q = tid & (MS - 1);
     const unsigned long long gmask = MS == 64 ? ~0ULL : ((1ULL << MS) - 1) << (lane & ~(MS - 1));
-    const double tol = 1e-11 * fmax(tnorm, 1.0);
+    const double tol = fine ? 2.0 * eps * fmax(fabs(glo), fabs(ghi)) : 1e-11 * fmax(tnorm, 1.0);
     const int idx = n - 1 - g;
     // joint first round: one point per thread over the whole interval
     int* cnt0 = reinterpret_cast<int*>(sh + L.part);
@@ -1006,7 +1017,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
   }
   // inverse iteration leaves vectors of eigenvalues more than 1e-3 ||T|| apart
   // orthogonal to working accuracy; closer ones are orthonormalised together
-  bool cluster = false;
+  bool cluster = fine;
   for (int j = 1; j < K; ++j) cluster |= fabs(lam[j - 1] - lam[j]) < 1e-3 * tnorm;
   if (cluster) {
     double* qb = sh + L.part;   // the current vector, double-buffered
@@ -1073,7 +1084,7 @@ void eig_topk_dense(Ctx* c, const double* G, int n0, int K, double* lam_k, doubl
 #define TK_SMALL_CASE(NG)                                                                                       \
       case NG:                                                                                                  \
         hipLaunchKernelGGL(k_syev_small<NG>, dim3(1), dim3(SM_THREADS), (size_t)SL.total * 8, c->stream, G, n0, \
-                           Ke, K, SL, lam_k, VK);                                                               \
+                           Ke, K, small_is_fine(n0, Ke), SL, lam_k, VK);                                        \
         break;
       TK_SMALL_CASE(1) TK_SMALL_CASE(2) TK_SMALL_CASE(3) TK_SMALL_CASE(4)
       TK_SMALL_CASE(5) TK_SMALL_CASE(6) TK_SMALL_CASE(7) TK_SMALL_CASE(8)
