@@ -870,8 +870,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
   // 3. eigenvectors of T by inverse iteration, lane j of the first row of 16
   // for vector j: one LU factorisation of T - lambda I with partial pivoting,
   // two solves from the seeded start vector (the first forward elimination runs
-  // with the factorisation).  Step i of vector j keeps {1/u0, multiplier} and
-  // {u1/u0, u2/u0}; the multiplier's last bit says whether the rows were swapped.
+  // with the factorisation).  Step i of vector j keeps {multiplier, u2/u0} in P
+  // and {1/u0, u1/u0} in U; the rows were swapped where u2/u0 is not +0 (a zero
+  // of a swapped row is stored as -0).
   if (tid < 16) {
     const int j = min(tid, K - 1);
     double lj = lam[j];
@@ -892,9 +893,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
       const double r = rcp2(p0);
       const double m0 = (sw ? a0 : c) * r;
       const double y1 = sw ? nd : a1, x1 = sw ? a1 : nd;   // the pivot row's entry, the other row's
-      const long long mb = (__double_as_longlong(m0) & ~1LL) | (sw ? 1LL : 0LL);
-      P[16 * i] = double2{r, __longlong_as_double(mb)};
-      U[16 * i] = double2{y1 * r, sw ? ns * r : 0.0};
+      const double y2 = ns * r;
+      P[16 * i] = double2{m0, sw ? (y2 == 0.0 ? -0.0 : y2) : 0.0};
+      U[16 * i] = double2{r, y1 * r};
       z[16 * i] = sw ? nz : cur;
       cur = sw ? fma(-m0, nz, cur) : fma(-m0, cur, nz);
       a0 = fma(-m0, y1, x1);
@@ -921,47 +922,48 @@ __global__ __launch_bounds__(SM_THREADS) void k_syev_small(const double* __restr
       }
     }
     if (a0 == 0.0) a0 = tiny;
-    P[16 * nl] = double2{rcp2(a0), 0.0};
-    U[16 * nl] = double2{0.0, 0.0};
+    P[16 * nl] = double2{0.0, 0.0};
+    U[16 * nl] = double2{rcp2(a0), 0.0};
     z[16 * nl] = cur;
     constexpr int CH = 8;   // steps whose operands are loaded together
     for (int it = 0; it < 2; ++it) {
       if (it == 1) {   // forward elimination with the row interchanges
         cur = z[0];
-        auto fw = [&](int i, double nz, double ml) __attribute__((always_inline)) {
-          const bool sw = __double_as_longlong(ml) & 1;
+        auto fw = [&](int i, double nz, double2 p) __attribute__((always_inline)) {
+          const bool sw = __double_as_longlong(p.y) != 0;
           z[16 * i] = sw ? nz : cur;
-          cur = sw ? fma(-ml, nz, cur) : fma(-ml, cur, nz);
+          cur = sw ? fma(-p.x, nz, cur) : fma(-p.x, cur, nz);
         };
         int i = 0;
         for (; i + CH <= nl; i += CH) {
-          double nz[CH], ml[CH];
+          double nz[CH];
+          double2 p[CH];
 #pragma unroll
-          for (int s = 0; s < CH; ++s) { nz[s] = z[16 * (i + s + 1)]; ml[s] = P[16 * (i + s)].y; }
+          for (int s = 0; s < CH; ++s) { nz[s] = z[16 * (i + s + 1)]; p[s] = P[16 * (i + s)]; }
 #pragma unroll
-          for (int s = 0; s < CH; ++s) fw(i + s, nz[s], ml[s]);
+          for (int s = 0; s < CH; ++s) fw(i + s, nz[s], p[s]);
         }
-        for (; i < nl; ++i) fw(i, z[16 * (i + 1)], P[16 * i].y);
+        for (; i < nl; ++i) fw(i, z[16 * (i + 1)], P[16 * i]);
         z[16 * nl] = cur;
       }
       // back substitution
       double z1 = 0.0, z2 = 0.0;
-      auto bw = [&](int i, double zi, double r, double2 u) __attribute__((always_inline)) {
-        const double s = fma(-u.x, z1, fma(-u.y, z2, zi * r));
+      auto bw = [&](int i, double zi, double2 u, double u2) __attribute__((always_inline)) {
+        const double s = fma(-u.y, z1, fma(-u2, z2, zi * u.x));
         z[16 * i] = s;
         z2 = z1;
         z1 = s;
       };
       int i = nl;
       for (; i - CH + 1 >= 0; i -= CH) {
-        double zi[CH], r[CH];
+        double zi[CH], u2[CH];
         double2 u[CH];
 #pragma unroll
-        for (int s = 0; s < CH; ++s) { zi[s] = z[16 * (i - s)]; r[s] = P[16 * (i - s)].x; u[s] = U[16 * (i - s)]; }
+        for (int s = 0; s < CH; ++s) { zi[s] = z[16 * (i - s)]; u2[s] = P[16 * (i - s)].y; u[s] = U[16 * (i - s)]; }
 #pragma unroll
-        for (int s = 0; s < CH; ++s) bw(i - s, zi[s], r[s], u[s]);
+        for (int s = 0; s < CH; ++s) bw(i - s, zi[s], u[s], u2[s]);
       }
-      for (; i >= 0; --i) bw(i, z[16 * i], P[16 * i].x, U[16 * i]);
+      for (; i >= 0; --i) bw(i, z[16 * i], U[16 * i], P[16 * i].y);
     }
   }
   __syncthreads();
