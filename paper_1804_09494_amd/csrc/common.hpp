@@ -348,7 +348,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
 void relabel_layout(Ctx* c, ModePlan& pl, int N, int n, const ModePlan* plans, int64_t m);
 void export_partition(Ctx* c, ModePlan& pl, int64_t m, int64_t* bin_ptr, int64_t* elem_order, int32_t* seg_bin,
                       int32_t* seg_slice, int64_t* seg_begin, uint8_t* seg_bad, tk_mem mem);
-int ttm_rows_cap(Ctx* c, int64_t tile_w);
+int ttm_rows_cap(const Ctx* c, int64_t tile_w);
 int ttm_tile_width(int N, const int32_t* K, int n);
 int64_t ttm_default_bin_nnz(int N, const int32_t* K, int n, int kernel);
 bool ttm_uses_mfma(int N, const int32_t* K, int n, const int* kp);

@@ -961,7 +961,9 @@ void uw_rows(Ctx* c, const float* Y, int64_t R, int khat, const double* W, int K
   const int64_t ntile = std::max<int64_t>(1, ceil_div(R, 16));
   const int waves = uw_waves(ntile);
   const size_t lds = uw_lds(khat, waves);
-  TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "Y W: Khat too large for LDS");
+  // (2 KB of room asked for beside W, as for the Grams of four waves)
+  TK_REQUIRE(sizeof(float) * 16 * (size_t)((khat + 15) & ~15) + 2048 <= c->lds_per_block && lds <= c->lds_per_block,
+             TK_ERR_UNSUPPORTED, "Y W: Khat too large for LDS");
   const FactorW w{W, nullptr, nullptr, 0, nullptr, nullptr};
   const dim3 g(uw_groups(ntile)), t(64 * waves);
   if (khat % 4 == 0)

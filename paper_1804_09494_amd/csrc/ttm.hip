@@ -1436,7 +1436,7 @@ int64_t ttm_default_bin_nnz(int N, const int32_t* K, int n, int kernel) {
   return 4096;
 }
 
-int ttm_rows_cap(Ctx* c, int64_t tile_w) {
+int ttm_rows_cap(const Ctx* c, int64_t tile_w) {
   // LDS budget for a bin's rows: about 40 KB so three bins share a CU, never
   // past the hardware limit.  Wide rows (k_ttm4_rows_mfma, Khat >= 512) leave
   // room for that kernel's staging (16 bytes per element) and tiles (12 KB).
@@ -1476,6 +1476,20 @@ static void ttm3w_launch(Ctx* c, const ModePlan& pl, const TtmArgs& a) {
   else
     hipLaunchKernelGGL((k_ttm3w_mfma<1, 1>), g, b, lds, c->stream, a, nseg_pad);
   TK_CHECK_LAUNCH();
+}
+
+// The limit on a bin of k_ttm4_mfma, which stages nothing: the one of the other
+// matrix-core kernels, under which a bin's elements (16 bytes each), rows of Khat
+// floats and tiles fit the LDS of a CU, in bins of at most the rows that
+// ttm_rows_cap gives that width.  The plan's own bins may hold more rows than
+// that; a plan of such bins is then judged by the least they could hold.
+static bool ttm4_bin_fits(const Ctx* c, const ModePlan& pl, int64_t m) {
+  const int64_t cap = std::min(pl.rows_cap, ttm_rows_cap(c, pl.khat));
+  const int64_t P = std::max<int64_t>(pl.P, ceil_div(pl.L_nz, cap - 2));
+  const int64_t E = P == pl.P ? pl.E_pad_max : ceil_div(m, P), R = P == pl.P ? pl.R_max : ceil_div(pl.L_nz, P);
+  const size_t lds = 3 * sizeof(int) * (size_t)((R + 3) & ~(int64_t)3) + 16 * (size_t)((E + 15) & ~(int64_t)15) +
+                     sizeof(float) * 4 * 768 + sizeof(float) * (size_t)R * (size_t)pl.khat;
+  return lds <= c->lds_per_block;
 }
 
 // TTM-chain of the elements of plan `pl` along mode n with FP32 factor copies
@@ -1527,13 +1541,14 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
              "TTM-chain: gathered values need the three-mode matrix-core kernel");
   if (!pl.whole_slices && c->opt.ttm_kernel == TK_TTM_FIBER && ttm_uses_fiber(N, K, n, kp)) {
     ttm_fiber_launch(c, pl, a, N);
-  } else if (!vector_only && !bf16 && ttm_uses_mfma(N, K, n, kp) && pl.P < TTM3_FEW_BINS) {
-    ttm3w_launch(c, pl, a);
   } else if (!vector_only && ttm_uses_mfma(N, K, n, kp)) {
     const int Epad = (int)((pl.E_pad_max + 15) & ~(int64_t)15);
+    // one limit on a bin whichever kernel its number of bins leads to
     const size_t lds = 12 * (size_t)Epad + sizeof(float) * 512 + sizeof(float) * (size_t)pl.R_max * (size_t)pl.khat;
     TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
-    if (val_order) {
+    if (!bf16 && pl.P < TTM3_FEW_BINS) {
+      ttm3w_launch(c, pl, a);
+    } else if (val_order) {
       TK_REQUIRE(!bf16, TK_ERR_UNSUPPORTED, "TTM-chain: gathered values take the FP32 tiles");
       hipLaunchKernelGGL((k_ttm3_mfma<false, true>), dim3((unsigned)pl.P), dim3(64), lds, c->stream, a, Epad);
     } else if (bf16) {
@@ -1558,6 +1573,7 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
       else
         bf16 ? go(k_ttm4_rows_mfma<2, true>) : go(k_ttm4_rows_mfma<2, false>);
     } else {
+    TK_REQUIRE(ttm4_bin_fits(c, pl, m), TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
     const size_t row = sizeof(float) * (((size_t)pl.khat + 3) & ~(size_t)3);
     const size_t base = 3 * sizeof(int) * (size_t)nseg_pad + sizeof(float) * TTM4_WAVES * TTM4_TILE + (TTM4_WAVES - 1) * row;
     // Rows staged while three bins still share a CU; longer ones (Khat above
