@@ -677,7 +677,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
                      keep_order ? pl.elem_order.as<uint32_t>() : nullptr,
                      vals ? nullptr : pl.order_pad.as<uint32_t>());
   TK_CHECK_LAUNCH();
-  // Worth it from eight pieces per shared slice (Zipf 0.8/1.2/1.5 over 4e6 x 4e6 x
+  // (Only bins with a shared piece move.)  Worth it from eight pieces per shared slice (Zipf 0.8/1.2/1.5 over 4e6 x 4e6 x
   // 2e6, 2e8 draws: 26 pieces 2.41 -> 1.83 ms, 108 pieces 2.19 -> 1.45 ms, L2
   // misses halved); with fewer the ranges are wide (3.8 to 5.8 pieces: between
   // 1% faster and 2% slower).  Below about 4096 bins all of them run at once.
@@ -687,7 +687,7 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   // of a range then stay in L2 (5e7 observations, Zipf 1.0, 16 pieces a slice and
   // more: adjoint 5.87 -> 5.17 ms; ordering each slice by its widest other mode
   // instead gave 5.68 and took 30% longer to load).
-  if (N == 3 && P >= 4096 && pl.n_slots >= 8 * nbad) {
+  if (N == 3 && P >= 4096 && nbad > 0 && pl.n_slots >= 8 * nbad) {
     const int64_t range = vals ? dims[n == 0 ? 1 : 0] : m;
     Buf bk(c, 4 * (size_t)P), bk2(c, 4 * (size_t)P), bv(c, 4 * (size_t)P);
     pl.bin_order.alloc(c, 4 * (size_t)P);
