@@ -257,8 +257,8 @@ struct Ctx {
 inline void Buf::alloc(Ctx* c, size_t bytes) {
   release();
   ctx_ = c;
-  bytes_ = bytes;
   p_ = bytes ? c->alloc_raw(bytes, &cap_) : nullptr;
+  bytes_ = bytes;   // after the call: a failed allocation leaves an empty buffer
 }
 
 inline void Buf::release() {
