@@ -272,6 +272,18 @@ inline void ensure(Ctx* c, Buf& b, size_t bytes) {
   if (b.bytes() < bytes) b.alloc(c, bytes);
 }
 
+// f() takes memory that only makes later calls faster: false where there is none.
+template <class F>
+inline bool if_room(F&& f) {
+  try {
+    f();
+    return true;
+  } catch (const Error& e) {
+    if (e.status != TK_ERR_OOM) throw;
+    return false;
+  }
+}
+
 template <class T>
 inline void h2d(Ctx* c, T* dst, const T* src, size_t n) {
   if (n) TK_HIP(hipMemcpyAsync(dst, src, n * sizeof(T), hipMemcpyHostToDevice, c->stream));

@@ -99,21 +99,29 @@ void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t 
     o.F32[j].alloc(c, sizeof(float) * (size_t)dims[j] * o.kp[j]);
   }
   o.gl.alloc(c, sizeof(float) * (size_t)std::max<int64_t>(n_obs, 1));
-  o.eval_pos.release();
-  if (eval_on_mfma(o) && n_obs >= EVAL_TWO_PASS && o.plan[eval_mode(o)].L_nz <= EVAL_TWO_PASS_SLICES) {
-    const ModePlan& pl = o.plan[eval_mode(o)];
-    o.eval_pos.alloc(c, sizeof(uint32_t) * (size_t)n_obs);
-    ensure(c, o.gl, sizeof(float) * (size_t)pl.m_pad);
-    hipLaunchKernelGGL(k_invert, dim3(grid_for(pl.m_pad, 256)), dim3(256), 0, c->stream,
-                       pl.order_pad.as<uint32_t>(), pl.m_pad, o.eval_pos.as<uint32_t>());
-    TK_CHECK_LAUNCH();
-  }
   o.Yg.alloc(c, sizeof(float) * (size_t)maxY);
   int64_t pk = 1;
   for (int j = 0; j < N; ++j) pk *= ranks[j];
   o.G32.alloc(c, sizeof(float) * (size_t)pk);
   o.Kd.alloc(c, sizeof(int32_t) * 8);
   h2d(c, o.Kd.as<int32_t>(), o.K, 8);
+  // the two-pass forward's table, after what every call needs: without room for
+  // it the forward scatters its values
+  o.eval_pos.release();
+  if (eval_on_mfma(o) && n_obs >= EVAL_TWO_PASS && o.plan[eval_mode(o)].L_nz <= EVAL_TWO_PASS_SLICES) {
+    const ModePlan& pl = o.plan[eval_mode(o)];
+    if (if_room([&] {
+          o.eval_pos.alloc(c, sizeof(uint32_t) * (size_t)n_obs);
+          ensure(c, o.gl, sizeof(float) * (size_t)pl.m_pad);
+        })) {
+      hipLaunchKernelGGL(k_invert, dim3(grid_for(pl.m_pad, 256)), dim3(256), 0, c->stream,
+                         pl.order_pad.as<uint32_t>(), pl.m_pad, o.eval_pos.as<uint32_t>());
+      TK_CHECK_LAUNCH();
+    } else {
+      o.eval_pos.release();
+      ensure(c, o.gl, sizeof(float) * (size_t)n_obs);
+    }
+  }
   c->sync();
   c->have_obs = true;
 }

@@ -688,16 +688,20 @@ void build_plan(Ctx* c, ModePlan& pl, int N, int n, const int64_t* dims, int64_t
   // more: adjoint 5.87 -> 5.17 ms; ordering each slice by its widest other mode
   // instead gave 5.68 and took 30% longer to load).
   if (N == 3 && P >= 4096 && nbad > 0 && pl.n_slots >= 8 * nbad) {
+    // (without room for the sort the bins keep their order)
     const int64_t range = vals ? dims[n == 0 ? 1 : 0] : m;
-    Buf bk(c, 4 * (size_t)P), bk2(c, 4 * (size_t)P), bv(c, 4 * (size_t)P);
-    pl.bin_order.alloc(c, 4 * (size_t)P);
-    hipLaunchKernelGGL(k_bin_order_key, dim3(grid_for(P, B)), dim3(B), 0, c->stream, pl.seg_ptr.as<int32_t>(),
-                       pl.seg_begin.as<int64_t>(), pl.seg_pbegin.as<int64_t>(), pl.seg_slot.as<int32_t>(),
-                       vals ? pl.lay_idx[0].as<uint32_t>() : pl.order_pad.as<uint32_t>(), P, range,
-                       bk.as<uint32_t>(), bv.as<uint32_t>());
-    TK_CHECK_LAUNCH();
-    sort_pairs_u32(c, bk.as<uint32_t>(), bk2.as<uint32_t>(), bv.as<uint32_t>(), pl.bin_order.as<uint32_t>(), P,
-                   bits_for_len(range));
+    if (!if_room([&] {
+          Buf bk(c, 4 * (size_t)P), bk2(c, 4 * (size_t)P), bv(c, 4 * (size_t)P);
+          pl.bin_order.alloc(c, 4 * (size_t)P);
+          hipLaunchKernelGGL(k_bin_order_key, dim3(grid_for(P, B)), dim3(B), 0, c->stream, pl.seg_ptr.as<int32_t>(),
+                             pl.seg_begin.as<int64_t>(), pl.seg_pbegin.as<int64_t>(), pl.seg_slot.as<int32_t>(),
+                             vals ? pl.lay_idx[0].as<uint32_t>() : pl.order_pad.as<uint32_t>(), P, range,
+                             bk.as<uint32_t>(), bv.as<uint32_t>());
+          TK_CHECK_LAUNCH();
+          sort_pairs_u32(c, bk.as<uint32_t>(), bk2.as<uint32_t>(), bv.as<uint32_t>(), pl.bin_order.as<uint32_t>(),
+                         P, bits_for_len(range));
+        }))
+      pl.bin_order.release();
   }
   c->sync();
   pl.row_of = std::move(row_of);

@@ -68,3 +68,59 @@ def test_smaller_call_after_a_failed_one(tk):
     assert rel_fro(Y, want) <= 1e-5
     ctx.close()
     assert not h.live
+
+
+def test_observations_without_room_for_the_two_pass_table(tk):
+    """The forward's table of positions (4 bytes per observation) is the last thing
+    tk_load_obs takes; a byte too little for it leaves the one-pass form, with the
+    same values."""
+    import torch
+    dims, ranks, m = (400_000, 300, 20), (4, 3, 5), (1 << 20) + 77
+    print("case", dims, flush=True)
+    idx = [torch.from_numpy(i).cuda() for i in synth.coordinates(973, dims, m, "zipf", (0.3, 0.5, 0.5))]
+    rng = np.random.default_rng(974)
+    G = torch.from_numpy(rng.standard_normal(int(np.prod(ranks))).astype(np.float32)).cuda()
+    F = [torch.from_numpy(rng.standard_normal((L, K)).astype(np.float32)).cuda() for L, K in zip(dims, ranks)]
+    full = Hook(tk)
+    full.ctx.load_obs(idx, dims, ranks)
+    assert full.used == full.peak - 4           # the end of the call needs most (with a flag of 4 bytes)
+    want = full.ctx.tucker_eval(G, F).cpu().numpy()
+    total = full.peak
+    full.ctx.close()
+    h = Hook(tk)
+    h.budget = total - 1
+    h.ctx.load_obs(idx, dims, ranks)
+    assert h.used <= total - 4 * m
+    np.testing.assert_array_equal(h.ctx.tucker_eval(G, F).cpu().numpy(), want)
+    h.ctx.close()
+    assert not h.live and not full.live
+
+
+def test_ranks_without_room_for_the_bin_order(tk):
+    """The sort of the bins' launch order comes while the plan is at its largest; a
+    byte too little for it leaves the bins as they are numbered."""
+    dims, ranks = (3000, 2000, 700), (10, 10, 10)
+    idx, vals = zipf_tensor(dims, 90_000, s=(0.4, 1.3, 1.5), seed=83)
+    dims = tuple(int(i.max()) + 1 for i in idx)
+    print("case", dims, flush=True)
+    F = [synth.normal(84, 200 + n, d * k).reshape(d, k) for n, (d, k) in enumerate(zip(dims, ranks))]
+    Y, peak, used = [], 0, 0
+    for tight in (False, True):
+        h = Hook(tk)
+        h.ctx.set_options(wg_nnz_target=16, keep_elem_order=0)
+        h.ctx.load_coo(idx, vals, dims)
+        if tight:
+            h.budget = peak - 1
+        h.peak = 0
+        h.ctx.set_ranks(ranks)
+        if tight:
+            assert h.used < used        # an order fewer
+        peak, used = h.peak, h.used
+        h.budget = 1 << 60
+        for n in range(3):
+            h.ctx.set_factor(n, F[n])
+        Y.append([h.ctx.ttm_chain(n)[0] for n in range(3)])
+        h.ctx.close()
+        assert not h.live
+    for a, b in zip(*Y):
+        np.testing.assert_array_equal(a, b)
