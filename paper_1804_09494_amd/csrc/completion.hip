@@ -215,8 +215,9 @@ __global__ void k_pad_copy(const float* __restrict__ src, int64_t L, int K, floa
 //     multiplies it with its own quad of F_b[l_b(i)] (one more 16-byte load) and
 //     adds over the four lane groups.
 // A block ends with its segment; the next one starts there.  Factors are the
-// 16-float padded copies.  Each observation's value goes to its own index
-// (order_pad); padding positions are skipped.
+// 16-float padded copies.  SCATTER: each observation's value goes to its own
+// index (order_pad), padding positions are skipped; else the values stay in
+// layout order, padding positions included, for k_take.
 // 5e7 observations, ranks 16, 500000 x 500000 x 50000, Zipf 1.0: 1.13 ms and the
 // second pass 0.2 (one wave per bin, no row in flight while a block is worked
 // on, four gathers of F_b's entries and scattered writes: 3.33 ms); 2e5

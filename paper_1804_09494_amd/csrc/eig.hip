@@ -89,13 +89,6 @@ __device__ __forceinline__ double row16_sum(double x) {
   return x;
 }
 
-__device__ __forceinline__ double lane_val(double x, int l) {   // x of lane l (l wave-uniform)
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 // Sum of x over the wave, in every lane: rows of 16, then rows and halves
 // exchanged (each swap leaves the two operands' sums over both places).
 __device__ __forceinline__ double wave_sum_u(double x) {
@@ -504,8 +497,6 @@ constexpr int SM_N = 128;
 constexpr int SM_WAVES = 4;
 constexpr int SM_THREADS = 64 * SM_WAVES;
 
-__device__ __forceinline__ double rl(double x, int l) { return lane_val(x, l); }
-
 struct SmallLayout {
   int64_t v, d, e, tau, lam, Z, lu, part, row, total;
 };
@@ -555,7 +546,7 @@ __device__ __forceinline__ double rcp2(double x) {
 // value at column J (wave-uniform) of a row held as NC registers
 template <int NC>
 __device__ __forceinline__ double col_of(const double (&x)[NC], int J) {
-  const double a = rl(x[0], J & 63), b = rl(x[NC - 1], J & 63);   // both read: a select of two registers
+  const double a = lane_value(x[0], J & 63), b = lane_value(x[NC - 1], J & 63);   // both read: a select of two registers
   return J < 64 ? a : b;                                          // by index would put them in memory
 }
 

@@ -7,11 +7,12 @@
 // rows of Y live in LDS for the whole bin; after the bin, rows of slices the
 // bin owns alone are written straight to Y and rows of slices split over
 // several bins go to a partial slot, which the fixup kernels sum in bin order.
-// Four kernels:
+// Five kernels:
 //   * k_ttm3_mfma: three modes, other ranks <= 16, on the matrix cores;
 //   * k_ttm3w_mfma: three modes, other ranks <= 32, one above 16, likewise, and
 //     smaller ranks where there are few bins;
 //   * k_ttm4_mfma: four modes, other ranks <= 16, on the matrix cores;
+//   * k_ttm4_rows_mfma: the same where K_b K_c <= 32;
 //   * k_ttm_cols:  every other shape, on the vector ALUs.
 // None of them uses atomics: every sum runs in a fixed order.
 #include <mutex>
@@ -1576,27 +1577,27 @@ void ttm_run(Ctx* c, const ModePlan& pl, int N, int n, const int32_t* K, const f
     TK_REQUIRE(ttm4_bin_fits(c, pl, m), TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
     const size_t row = sizeof(float) * (((size_t)pl.khat + 3) & ~(size_t)3);
     const size_t base = 3 * sizeof(int) * (size_t)nseg_pad + sizeof(float) * TTM4_WAVES * TTM4_TILE + (TTM4_WAVES - 1) * row;
-    // Rows staged while three bins still share a CU; longer ones (Khat above
-    // about 1300) go straight from the accumulators: the row would cost a wave
+    // Rows staged while three bins still share a CU, which they do up to five tiles
+    // (Khat <= 1280) whatever the ranks; longer ones (Khat above about 1300) go straight from the accumulators: the row would cost a wave
     // per SIMD (ranks 16: 1.48 ms for four chains of 1e6 elements, 2.76 with the
     // bin's rows kept)
-    const bool stage = 3 * (base + TTM4_WAVES * row) <= c->lds_per_block;
+    const int tiles = ttm4_tiles(a.Kj[1], a.Kj[2]);
+    const bool stage = tiles <= 5 || 3 * (base + TTM4_WAVES * row) <= c->lds_per_block;
     const size_t lds = stage ? base + TTM4_WAVES * row : base;
     TK_REQUIRE(lds <= c->lds_per_block, TK_ERR_UNSUPPORTED, "TTM-chain: bin too large for LDS");
     auto go = [&](auto direct, auto staged) {
       hipLaunchKernelGGL((stage ? staged : direct), g, b, lds, c->stream, a, nseg_pad);
     };
-    switch (ttm4_tiles(a.Kj[1], a.Kj[2])) {
-#define TK_TTM4_CASE(NT)                                                        \
-      case NT:                                                                  \
-        if (bf16)                                                               \
-          go(k_ttm4_mfma<NT, true, false>, k_ttm4_mfma<NT, true, true>);        \
-        else                                                                    \
-          go(k_ttm4_mfma<NT, false, false>, k_ttm4_mfma<NT, false, true>);      \
+    switch (tiles) {
+#define TK_TTM4_CASE(NT, DIRECT)                                                                     \
+      case NT:                                                                                       \
+        bf16 ? go(k_ttm4_mfma<NT, true, DIRECT>, k_ttm4_mfma<NT, true, true>)                        \
+             : go(k_ttm4_mfma<NT, false, DIRECT>, k_ttm4_mfma<NT, false, true>);                     \
         break;
-      TK_TTM4_CASE(3) TK_TTM4_CASE(4) TK_TTM4_CASE(5) TK_TTM4_CASE(6)
-      TK_TTM4_CASE(7) TK_TTM4_CASE(8) TK_TTM4_CASE(9) TK_TTM4_CASE(10) TK_TTM4_CASE(11) TK_TTM4_CASE(12)
-      TK_TTM4_CASE(13) TK_TTM4_CASE(14) TK_TTM4_CASE(15) TK_TTM4_CASE(16)
+      TK_TTM4_CASE(3, true) TK_TTM4_CASE(4, true) TK_TTM4_CASE(5, true)
+      TK_TTM4_CASE(6, false) TK_TTM4_CASE(7, false) TK_TTM4_CASE(8, false) TK_TTM4_CASE(9, false)
+      TK_TTM4_CASE(10, false) TK_TTM4_CASE(11, false) TK_TTM4_CASE(12, false) TK_TTM4_CASE(13, false)
+      TK_TTM4_CASE(14, false) TK_TTM4_CASE(15, false) TK_TTM4_CASE(16, false)
 #undef TK_TTM4_CASE
       default: fail(TK_ERR_UNSUPPORTED, "four-mode TTM: rank above 16");
     }
