@@ -106,7 +106,10 @@ typedef struct {
   int32_t sweep;                  /* tk_sweep (default Gauss-Seidel: mode n uses factors refined earlier in the invocation) */
   int64_t wg_nnz_target;          /* target elements per bin; 0 (default) = per kernel: 448 for the
                                      three-mode matrix-core TTM-chain, 1024 for the four-mode one and
-                                     for the completion adjoint, 4096 otherwise */
+                                     for the completion adjoint, 4096 otherwise.  Bins whose elements
+                                     and rows exceed the LDS of a compute unit (about 9,000 elements
+                                     with four modes, 13,000 with three) give TK_ERR_UNSUPPORTED from
+                                     the matrix-core TTM-chains of ranks up to 16 */
   int32_t lds_rows_cap;           /* max slices per bin; 0 = from the LDS budget */
   int32_t refine;                 /* BF16 only: 1 = the last invocation runs in FP32 (default 1) */
   int64_t mem_limit_bytes;        /* 0 = no limit; plans above it fail with TK_ERR_OOM before allocating */

@@ -533,7 +533,8 @@ static SmallLayout small_layout(int n) {
 // columns.  Larger problems are taken to FP64
 // resolution as in the general solver: the Rayleigh-Ritz steps of the block-Krylov solver
 // for ranks from 12 on are among them, and an eigenvalue's error there is a
-// floor of the residual that a caller's eig_tol is compared with.
+// floor of the residual that a caller's eig_tol is compared with (n = 121, K = 11:
+// 196 us to 1e-11, 213 to FP64 resolution, 1517 in the general solver).
 static bool small_is_fine(int n, int K) { return n * (n + 6 * K) > 16640; }
 
 // Newton-refined hardware reciprocal
