@@ -63,6 +63,8 @@ void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t 
     o.plan[j] = ModePlan();
     o.F32[j].release();
   }
+  o.gl.release();
+  o.eval_pos.release();
   o.N = N;
   o.n_obs = n_obs;
   for (int j = 0; j < 8; ++j) {
@@ -107,7 +109,6 @@ void load_obs(Ctx* c, int N, const int64_t* dims, const int32_t* ranks, int64_t 
   h2d(c, o.Kd.as<int32_t>(), o.K, 8);
   // the two-pass forward's table, after what every call needs: without room for
   // it the forward scatters its values
-  o.eval_pos.release();
   if (eval_on_mfma(o) && n_obs >= EVAL_TWO_PASS && o.plan[eval_mode(o)].L_nz <= EVAL_TWO_PASS_SLICES) {
     const ModePlan& pl = o.plan[eval_mode(o)];
     if (if_room([&] {

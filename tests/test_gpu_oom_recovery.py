@@ -96,6 +96,25 @@ def test_observations_without_room_for_the_two_pass_table(tk):
     assert not h.live and not full.live
 
 
+def test_loading_observations_again(tk):
+    """What the observations before leave during the next load: the work buffers for
+    the adjoint's Y (300 rows of 15 floats at most) and the core, not the forward's
+    table and values (8 bytes per observation and padding)."""
+    import torch
+    dims, ranks, m = (300, 200, 20), (4, 3, 5), (1 << 20) + 77
+    print("case", dims, flush=True)
+    idx = [torch.from_numpy(i).cuda() for i in synth.coordinates(975, dims, m, "zipf", (0.3, 0.5, 0.5))]
+    h = Hook(tk)
+    h.ctx.load_obs(idx, dims, ranks)
+    first = h.peak
+    assert first > h.used + 4               # the partition of the observations needs most
+    h.peak = 0
+    h.ctx.load_obs(idx, dims, ranks)
+    assert h.peak - first <= 4 * (300 * 15 + 60 + 8)
+    h.ctx.close()
+    assert not h.live
+
+
 def test_ranks_without_room_for_the_bin_order(tk):
     """The sort of the bins' launch order comes while the plan is at its largest; a
     byte too little for it leaves the bins as they are numbered."""
