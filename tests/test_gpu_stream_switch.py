@@ -53,3 +53,38 @@ def test_reload_after_switch_leaves_queued_chains_alone(tk, noalloc):
         ref = tk.TuckerContext(0)
     load(ref, second)
     np.testing.assert_array_equal(got, ref.ttm_chain(0)[0])
+
+
+def test_switch_inside_a_capture(tk):
+    """The context moves to the capturing stream inside the capture, and back after
+    it; every replay gives the eager rows, with eager work, releases and new
+    factors between them."""
+    import torch
+    dims, ranks, nnz = (3000, 2000, 700), (10, 8, 5), 200_000
+    print("case", dims, flush=True)
+    t = _tensor(dims, nnz, 904)
+    F = [[synth.normal(s, 200 + n, d * k).reshape(d, k) for n, (d, k) in enumerate(zip(dims, ranks))]
+         for s in (905, 906)]
+    torch.cuda.synchronize()
+    ctx, other = tk.TuckerContext(0), tk.TuckerContext(0)
+    for c in (ctx, other):
+        c.load_coo(*t, dims)
+        c.set_ranks(ranks)
+    Y = torch.empty(ctx.ttm_shape(0), device="cuda:0")
+    home = torch.cuda.current_stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ctx.set_stream(torch.cuda.current_stream())
+        ctx.ttm_chain_noalloc(0, Y)
+    ctx.set_stream(home)
+    for rep in range(4):
+        for n in range(3):
+            ctx.set_factor(n, F[rep % 2][n])
+            other.set_factor(n, F[rep % 2][n])
+        want = other.ttm_chain(0)[0]
+        ctx.ttm_chain(1)               # eager work on the context between the replays
+        Y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(Y.cpu().numpy(), want)
+        np.testing.assert_array_equal(ctx.ttm_chain(0)[0], want)
