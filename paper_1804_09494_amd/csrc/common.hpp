@@ -176,7 +176,7 @@ struct ObsSet {
   ModePlan plan[8];  // Lite partition of the observations along each mode (adjoint TTM-chain)
   Buf F32[8];        // padded FP32 copies of the caller's factors
   int kp[8] = {0};
-  Buf gl;            // float[n_obs] upstream gradient in one mode's layout order
+  Buf gl;            // float[n_obs or m_pad] in one mode's layout order: upstream gradient, two-pass forward's values
   Buf Yg;            // float[max R_n x Khat_n]
   Buf G32;           // float[prod K] core copy
   Buf Kd;            // int32[8] the ranks
